@@ -1151,6 +1151,8 @@ size_t scan_lds_bytes(int fam, int dk, int chunk, bool f32io, int nb, bool summa
 // the output correction of its pieces (ssd_scan.hip)
 bool ssd_scan_supported(int dk, int chunk, bool f32io, int dv);
 hipError_t launch_ssd_scan(int dk, const ScanArgs& a, hipStream_t st);
+// the same with two adjacent 64-row units per workgroup, for batches that fill the GPU
+hipError_t launch_ssd_pair(int dk, const ScanArgs& a, hipStream_t st);
 struct SsdCorrectArgs {
     const int32_t* cu;     // the requests' token ranges (as the scan's cu)
     int32_t n_seq;

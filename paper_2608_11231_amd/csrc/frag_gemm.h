@@ -218,6 +218,11 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
     return uint4{v[0], v[1], v[2], v[3]};
 }
 
+__device__ __forceinline__ void buf_store8(__amdgpu_buffer_rsrc_t r, uint32_t off, bf16x4 v) {
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, off, 0, 0);
+}
+
 template <int CH, int DK, bool F32IO, int NTH>
 struct KQTile {
     static constexpr int UPR = DK / 8;                // units per row
@@ -310,7 +315,7 @@ struct TileRegs {
         for (int i = 0; i < PER; ++i) {
             const int idx = tid + i * NTH;
             const int t = idx / VPR, cv = idx % VPR;
-            r[i] = buf_load16(rs, idx < NV ? chunk_off + (uint32_t)t * row_bytes + 16u * cv : 0xffffffffu);
+            r[i] = buf_load16(rs, NV % NTH == 0 || idx < NV ? chunk_off + (uint32_t)t * row_bytes + 16u * cv : 0xffffffffu);
         }
     }
     // row-major into dst (row stride ds elements; lo plane at dst + pofs for fp32 io)
@@ -318,7 +323,7 @@ struct TileRegs {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int idx = tid + i * NTH;
-            if (idx >= NV) continue;
+            if (NV % NTH != 0 && idx >= NV) continue;
             const int t = idx / VPR, c = (idx % VPR) * EPV;
             if (!F32IO) {
                 *reinterpret_cast<uint4*>(dst + t * ds + c) = r[i];

@@ -112,13 +112,34 @@ ScanArgs base_args(const lkv_layer* L, const lkv_tokens* T) {
     return a;
 }
 
-// Mamba-2 scans and block summaries can run on ssd_scan_kernel where it
-// covers the shapes (bf16 io, 64-token chunks, dk >= 32, dv a multiple of 64):
-// LKV_SSD_SCAN_KERNEL=1 selects it, otherwise the shared chunk kernel runs
-// (the two give identical bits).
-bool use_ssd_scan(const lkv_layer* L) {
-    return L->family == LKV_SSD && env_int("LKV_SSD_SCAN_KERNEL", 0) == 1 &&
-           ssd_scan_supported(L->dk, L->chunk, L->io_dtype == LKV_F32, L->dv);
+// Mamba-2 scans and block summaries run on one of three kernels with identical
+// bits: the shared chunk kernel, ssd_scan_kernel (eight waves on 64 state rows) and
+// ssd_pair_kernel (two adjacent 64-row units of a group per workgroup), the last
+// two where they cover the shapes (bf16 io, 64-token chunks, dk >= 32, dv a
+// multiple of 64; pairs need an even number of units per group).
+// By `units` of 64 rows (segments x heads x dv / 64):
+//  - pairs once every CU has work without them: from one unit per CU at dk = 128
+//    (16 requests x 64 heads of 64 x 128, 512-3072 tokens: 386 -> 213 us; 288
+//    units of 500-1500 tokens: 103 -> 78 us), from two at smaller dk, where two
+//    of the chunk kernel's workgroups share a CU (dk 64, 1024 units: 131 -> 88 us,
+//    512 units: 68 against 72 us).  With fewer units the serial chain counts, and a
+//    pair's chunk takes longer (64 units: 52 against 86 us).
+//  - ssd_scan_kernel at dk = 128 where the chunk kernel would need a second round
+//    of workgroups (they split rows until they fill the CUs, and overshoot) and
+//    one unit per CU does not: 192 units of 1536 tokens 99 -> 62 us, 96 units 32
+//    -> 22 us.  Within one round the chunk kernel is as fast or faster (64 units:
+//    52 against 58 us, 256 units: 64 against 63 us).
+// LKV_SSD_SCAN_KERNEL=1 forces ssd_scan_kernel, LKV_SSD_PAIR=1 / 0 pairs or none.
+enum SsdKernel { SSD_CHUNK, SSD_SCAN, SSD_PAIR };
+SsdKernel ssd_kernel(const lkv_layer* L, int64_t n_seq, bool summary) {
+    if (L->family != LKV_SSD || !ssd_scan_supported(L->dk, L->chunk, L->io_dtype == LKV_F32, L->dv)) return SSD_CHUNK;
+    if (env_int("LKV_SSD_SCAN_KERNEL", 0) == 1) return SSD_SCAN;
+    const int64_t per_group = L->dv / 64 * (int64_t)(L->h_v / L->h_qk), units = n_seq * L->h_qk * per_group;
+    const int forced = env_int("LKV_SSD_PAIR", -1);
+    if (per_group % 2 == 0 && (forced >= 0 ? forced == 1 : units > (L->dk == 128 ? 256 : 512))) return SSD_PAIR;
+    if (L->dk != 128 || units > 256 || forced >= 0) return SSD_CHUNK;
+    const int nb = pick_nw(L->family, L->dk, L->chunk, false, n_seq * L->h_v, L->dv, 0, summary);
+    return nb > 0 && units * 4 / nb > 256 ? SSD_SCAN : SSD_CHUNK;
 }
 
 // The sequence-parallel Mamba-2 scan as one pass over the pieces plus an
@@ -129,14 +150,14 @@ bool use_ssd_sp(const lkv_layer* L) {
            ssd_scan_supported(L->dk, L->chunk, L->io_dtype == LKV_F32, L->dv);
 }
 
-lkv_status ssd_scan(const lkv_layer* L, ScanArgs a, int64_t pairs, hipStream_t st) {
-    const int64_t units = pairs * (L->dv / 64);
+lkv_status ssd_scan(const lkv_layer* L, SsdKernel kernel, ScanArgs a, hipStream_t st) {
+    const int64_t units = (int64_t)a.n_seq * L->h_v * (L->dv / 64) / (kernel == SSD_PAIR ? 2 : 1);
     if (units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;
     a.tiles_b = L->dv / 64;
     a.tiles_m = 0;
     a.nb = 4;
     a.n_units = (int32_t)units;
-    return hip_status(launch_ssd_scan(L->dk, a, st));
+    return hip_status(kernel == SSD_PAIR ? launch_ssd_pair(L->dk, a, st) : launch_ssd_scan(L->dk, a, st));
 }
 
 hipError_t launch_scan(const lkv_layer* L, const ScanArgs& a, hipStream_t st) {
@@ -164,7 +185,8 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     a.out = out;
     a.S_final = S_final;
     a.summary = 0;
-    if (use_ssd_scan(L)) return ssd_scan(L, a, pairs, (hipStream_t)stream);
+    const SsdKernel sk = ssd_kernel(L, T->n_seq, false);
+    if (sk != SSD_CHUNK) return ssd_scan(L, sk, a, (hipStream_t)stream);
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, L->dv, 0, false);
     if (nw == 0) return LKV_E_UNSUPPORTED;
     const int64_t units = pairs * (L->dv / (16 * nw));
@@ -472,7 +494,8 @@ lkv_status lkv_block_summary(const lkv_layer* L, const lkv_tokens* T, float* B_o
         return hip_status(launch_ssd_lambda(T->cu, T->n_seq, T->n_tok, L->h_v, reinterpret_cast<const float*>(T->g),
                                             T->A, M_out, st));
     }
-    if (use_ssd_scan(L)) return ssd_scan(L, a, pairs, st);
+    const SsdKernel sk = ssd_kernel(L, T->n_seq, true);
+    if (sk != SSD_CHUNK) return ssd_scan(L, sk, a, st);
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, rows_b ? rows_b : rows_m,
                            rows_b ? rows_m : 0, true);
     if (nw == 0) return LKV_E_UNSUPPORTED;

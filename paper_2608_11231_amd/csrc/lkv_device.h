@@ -216,6 +216,29 @@ __device__ __forceinline__ int xcd_unit(int b, int n) {
     return x * q + min(x, r) + i;
 }
 
+// The segment with the rank-th most tokens (ties by index), n_seq <= 64: lane j
+// holds segment j's length, and counts the longer ones.  Every wave computes it
+// for itself (about 3 instructions per segment).  Kernels whose workgroups last
+// as long as their segment take the long segments first, so that a ragged
+// batch does not end on a few long ones.
+constexpr int RANK_SEGS = 64;
+__device__ __forceinline__ int ranked_segment(const int32_t* cu, int n_seq, int64_t n_tok, int rank, int lane) {
+    uint32_t len = 0;
+    if (lane < n_seq) {
+        int64_t t0 = cu[lane], t1 = cu[lane + 1];
+        t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
+        t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
+        len = (uint32_t)(t1 - t0) + 1;  // lanes past the last segment: 0, below every segment
+    }
+    int longer = 0;
+    for (int k = 0; k < n_seq; ++k) {
+        const uint32_t lk = (uint32_t)__builtin_amdgcn_readlane((int)len, k);
+        longer += (lk > len || (lk == len && k < lane)) ? 1 : 0;
+    }
+    const uint64_t hit = __ballot(lane < n_seq && longer == rank);
+    return __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
+}
+
 // Workgroup barrier for LDS traffic: waits for this wave's LDS operations only,
 // so global loads issued before it stay in flight across it (a __syncthreads
 // would also drain them).  Only for barriers that order LDS accesses.

@@ -378,6 +378,345 @@ __global__ __launch_bounds__(512) void ssd_scan_kernel(ScanArgs p) {
     }
 }
 
+// ---------------------------------------------------------------- pairs of units
+// The same scan for batches that fill the GPU.  There the eight-wave kernel and
+// the shared chunk kernel are bound by what a workgroup repeats per head: every
+// wave re-reads the chunk's B and C fragments from LDS for 16 state rows (LDS
+// reads alone take about 1900 cycles per chunk and 64 rows), and each head
+// stages B and C and forms C B^T anew, although all heads of a group share
+// them.  Here a workgroup of four waves owns two adjacent 64-row units of one
+// group (two heads at dv = 64): B and C are staged once for both, the products
+// C B^T are formed once and masked per unit, and each wave holds 32 state rows
+// (all dk columns), so every fragment it reads serves two row tiles and no
+// state parts cross waves.  LDS holds one chunk (69 KB at dk = 128), so two
+// workgroups share a CU and cover each other's barriers and load waits; the next
+// chunk waits in registers.  The products are issued in the other kernels' order:
+// identical bits.
+//
+// What bounds it: instruction issue of the two waves of a SIMD (per chunk and wave
+// 128 MFMAs and about 460 VALU instructions, 15 200 cycles for both workgroups of
+// a CU; LDS busy 25%, MFMA 22%).  16 requests x 64 heads of 64 x 128, 512-3072
+// tokens each: 386 us with the chunk kernel, 213 us here (2.3 TB/s of x, y and
+// states).  Eight waves of 16 rows instead of four of 32 read every fragment for
+// one row tile again and spilled: 417 us.
+template <int DK>
+struct SsdPairLds {
+    static constexpr int CH = 64, NTC = 4, NTK = DK / 16;
+    static constexpr int SK = DK + 16;    // kq_pos rows of B and C
+    static constexpr int SX = 128 + 16;   // X rows: the pair's 128 state rows
+    static constexpr int SB = 20, BLK = 16 * SB;
+    static constexpr int NPB = NTC * (NTC + 1) / 2;
+    static constexpr int GR = 4 * CH + 4;  // gate rows of one unit: dt | l | exp(l) | d | exp(l_C)
+    static constexpr size_t B_OFF = 0;
+    static constexpr size_t C_OFF = B_OFF + size_t(CH) * SK * 2;
+    static constexpr size_t X_OFF = C_OFF + size_t(CH) * SK * 2;
+    static constexpr size_t P_OFF = X_OFF + size_t(CH) * SX * 2;
+    static constexpr size_t G_OFF = P_OFF + size_t(2) * NPB * BLK * 2;
+    static constexpr size_t BYTES = G_OFF + size_t(2) * 2 * GR * 4;  // gate rows: two chunks, two units
+};
+
+template <int DK, bool OUT>
+__global__ __launch_bounds__(256, 2) void ssd_pair_kernel(ScanArgs p) {
+    using Ly = SsdPairLds<DK>;
+    constexpr int CH = Ly::CH, NTC = Ly::NTC, NTK = Ly::NTK, NKP = NTK / 2, RT = 2;
+    constexpr int SK = Ly::SK, SX = Ly::SX, SB = Ly::SB, BLK = Ly::BLK, NPB = Ly::NPB, GR = Ly::GR;
+    extern __shared__ __align__(16) char smem[];
+    bf16* const sB = reinterpret_cast<bf16*>(smem + Ly::B_OFF);
+    bf16* const sC = reinterpret_cast<bf16*>(smem + Ly::C_OFF);
+    bf16* const sX = reinterpret_cast<bf16*>(smem + Ly::X_OFF);
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, g = lane >> 4, c16 = lane & 15;
+    const int sub = w >> 1;  // the unit of the pair this wave's rows belong to
+    bf16* const sP = reinterpret_cast<bf16*>(smem + Ly::P_OFF) + sub * NPB * BLK;
+
+    // ---- work unit: a workgroup's time is its segment's length, so the longest
+    // segments go first (see ranked_segment); where every workgroup is resident
+    // at once (two per CU), the second one of a CU comes from the short end.
+    // The pairs of a segment are spread over the XCDs: B and C, which they
+    // share, are small next to x and y
+    const int n_pairs = p.n_units / p.n_seq;
+    int s = blockIdx.x / n_pairs, pr = blockIdx.x % n_pairs;
+    if (p.n_seq <= RANK_SEGS) {
+        if (p.n_units <= 512 && blockIdx.x >= 256) {
+            const int v = p.n_units - 1 - (blockIdx.x - 256);
+            s = v / n_pairs;
+            pr = v % n_pairs;
+        }
+        s = ranked_segment(p.cu, p.n_seq, p.n_tok, s, lane);
+    }
+    const int64_t rows_all = (int64_t)p.h_v * p.dv;
+    const int r0 = pr * 128;  // first state row of the pair among the h_v * dv rows
+    const int gu = w & 1, hg = (r0 + 64 * gu) / p.dv;  // the unit whose gate rows this wave may form, and its head
+    const int hq = (r0 / p.dv) / (p.h_v / p.h_qk);
+    int64_t t0 = p.cu[s], t1 = p.cu[s + 1];
+    t0 = t0 < 0 ? 0 : (t0 > p.n_tok ? p.n_tok : t0);
+    t1 = t1 < t0 ? t0 : (t1 > p.n_tok ? p.n_tok : t1);
+    const int nch = (int)((t1 - t0 + CH - 1) / CH);
+    const float Ah = p.A[hg];
+
+    // ---- chunk tiles: registers (a chunk ahead) -> LDS
+    KQTile<CH, DK, false, 256> pB, pC;
+    TileRegs<CH, 128, false, 256> pX;
+    uint32_t pdt = 0u;  // lane t's dt of the gate unit, two chunks ahead, raw bits until its use
+    float lam = 0.f;    // the segment's log-decay sum so far (block summaries' Lambda)
+    const uint32_t bc_rb = (uint32_t)p.h_qk * DK * 2, x_rb = (uint32_t)rows_all * 2, g_rb = (uint32_t)p.h_v * 4;
+    // A chunk's loads in two parts: x (HBM) a whole chunk ahead, B and C
+    // (read by every pair of the segment, so mostly L2 hits) after the products
+    // that need the most registers.  Past the last chunk the resources cover no
+    // rows and read as zeros, without a branch around the loads (it would copy
+    // their registers).
+    auto rows_of = [&](int ci, int64_t& c0) -> uint32_t {
+        c0 = t0 + (int64_t)(ci < nch ? ci : 0) * CH;
+        return ci < nch ? (uint32_t)((t1 - c0) < CH ? (t1 - c0) : CH) : 0u;
+    };
+    auto prefetch_x = [&](int ci) {
+        int64_t c0;
+        const uint32_t n = rows_of(ci, c0);
+        pX.load_buf(make_rsrc(reinterpret_cast<const char*>(p.v) + (c0 * rows_all + r0) * 2, n * x_rb), 0u, x_rb, tid);
+    };
+    auto prefetch_dt = [&](int ci) {
+        int64_t c0;
+        const uint32_t n = rows_of(ci, c0);
+        pdt = buf_load4(make_rsrc(reinterpret_cast<const char*>(p.g) + (c0 * p.h_v + hg) * 4, n * g_rb),
+                        (uint32_t)lane * g_rb);
+    };
+    auto prefetch_bc = [&](int ci) {
+        int64_t c0;
+        const uint32_t n = rows_of(ci, c0);
+        const int64_t bc_off = (c0 * p.h_qk + hq) * (int64_t)DK * 2;
+        pB.load_buf(make_rsrc(reinterpret_cast<const char*>(p.k) + bc_off, n * bc_rb), 0u, bc_rb, tid);
+        if constexpr (OUT)
+            pC.load_buf(make_rsrc(reinterpret_cast<const char*>(p.q) + bc_off, n * bc_rb), 0u, bc_rb, tid);
+    };
+    auto commit = [&]() {
+        pB.commit(sB, SK, 0, tid);
+        if constexpr (OUT) pC.commit(sC, SK, 0, tid);
+        pX.commit(sX, SX, 0, tid);
+    };
+    // Gate rows of a chunk from its dt, a chunk ahead: the last two waves, which
+    // build fewer output blocks, each form one unit's
+    auto gates = [&](int ci) {
+        if (w >= 2 && ci < nch) {
+            float* Gn = reinterpret_cast<float*>(smem + Ly::G_OFF) + (2 * (ci & 1) + gu) * GR;
+            const float dt = __builtin_bit_cast(float, pdt);
+            const float l = wave_incl_scan(Ah * dt);  // lanes past the segment hold dt = 0
+            const float lC = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, l), CH - 1));
+            Gn[lane] = dt;
+            Gn[CH + lane] = l;
+            Gn[2 * CH + lane] = __expf(l);
+            Gn[3 * CH + lane] = dt * __expf(lC - l);
+            if (lane == 0) Gn[4 * CH] = __expf(lC);
+            lam += lC;
+            asm volatile("" ::: "memory");
+        }
+    };
+
+    prefetch_dt(0);
+    prefetch_x(0);
+    prefetch_bc(0);
+
+    // ---- this wave's state: S[rt][nt] holds S[row(rt)][16nt + 4g + r]
+    auto row = [&](int rt) { return r0 + 32 * w + 16 * rt + c16; };
+    f32x4 S[RT][NTK];
+    {
+        int64_t init_row = s;
+        float init_fill = 0.f;
+        bool init_load = p.S_init != nullptr;
+        if (p.src) {
+            const int32_t id = p.src[s];
+            init_row = id;
+            if (id < 0 || id >= p.n_src) {
+                init_load = false;
+                init_fill = id == -1 ? 0.f : __builtin_nanf("");
+            }
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int64_t e0 = (init_row * rows_all + row(rt)) * DK + 4 * g;
+            if (init_load && p.init_bf16) {
+                uint2 q[NTK];
+#pragma unroll
+                for (int j = 0; j < NTK; ++j)
+                    q[j] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(p.S_init) + e0 + 16 * j);
+#pragma unroll
+                for (int j = 0; j < NTK; ++j) S[rt][j] = to_f32(__builtin_bit_cast(bf16x4, q[j]));
+            } else if (init_load) {
+#pragma unroll
+                for (int j = 0; j < NTK; ++j) S[rt][j] = *reinterpret_cast<const f32x4*>(p.S_init + e0 + 16 * j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NTK; ++j) S[rt][j] = f32x4{init_fill, init_fill, init_fill, init_fill};
+            }
+        }
+    }
+    const bf16x8 negI = neg_eye(g, c16), negIh = neg_eye_hi(g, c16);
+    // The state is used here on every path, so that none of its loads is still
+    // pending at the loop head (its wait there would drain the chunk's loads).
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < NTK; ++j) asm volatile("" : "+v"(S[rt][j]));
+
+    // output blocks of this wave: blocks i < nb of (row block, column block)
+    // (3,0-2) | (2,0-2) | (1,0-1) | (3,3) (0,0)
+    const int nb = w < 2 ? 3 : 2;
+    const int pa0 = w == 3 ? 3 : 3 - w, pa1 = w == 3 ? 0 : pa0;  // row block of blocks 0 and 2, and of block 1
+    const int pb0 = w == 3 ? 3 : 0, pb1 = w == 3 ? 0 : 1, pb2 = 2;
+
+    gates(0);
+    prefetch_dt(1);
+
+    for (int ci = 0; ci < nch; ++ci) {
+        const int64_t c0 = t0 + (int64_t)ci * CH;
+        const int n = (int)((t1 - c0) < CH ? (t1 - c0) : CH);
+        lds_barrier();  // the previous chunk is no longer read
+        commit();
+        prefetch_x(ci + 1);
+        lds_barrier();  // chunk ci staged
+        const float* G = reinterpret_cast<const float*>(smem + Ly::G_OFF) + (2 * (ci & 1) + sub) * GR;
+        f32x4 OT[RT][NTC];
+        if constexpr (OUT) {
+            // S C^T (transposed outputs), and this wave's share of C B^T
+            f32x4 acc[3] = {zero4(), zero4(), zero4()};
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int mt = 0; mt < NTC; ++mt) OT[rt][mt] = zero4();
+            const bf16* Cr = sC + c16 * SK + 8 * g;
+            const bf16* Br = sB + c16 * SK + 8 * g;
+#pragma unroll
+            for (int kp = 0; kp < NKP; ++kp) {
+                bf16x8 cf[NTC], fa[2], fb[3];
+#pragma unroll
+                for (int mt = 0; mt < NTC; ++mt) cf[mt] = lds8(Cr + 16 * mt * SK + 32 * kp);
+                fa[0] = lds8(Cr + 16 * pa0 * SK + 32 * kp);
+                fa[1] = lds8(Cr + 16 * pa1 * SK + 32 * kp);
+                fb[0] = lds8(Br + 16 * pb0 * SK + 32 * kp);
+                fb[1] = lds8(Br + 16 * pb1 * SK + 32 * kp);
+                fb[2] = lds8(Br + 16 * pb2 * SK + 32 * kp);  // unused when nb = 2
+                __builtin_amdgcn_sched_barrier(0);
+                // the state enters the outputs as its bf16 hi part
+                bf16x4 s0[RT], s1[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    s0[rt] = to_bf16(S[rt][2 * kp]);
+                    s1[rt] = to_bf16(S[rt][2 * kp + 1]);
+                }
+#pragma unroll
+                for (int mt = 0; mt < NTC; ++mt)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) OT[rt][mt] = mma32(s0[rt], s1[rt], cf[mt], OT[rt][mt]);
+                acc[0] = mma32(fa[0], fb[0], acc[0]);
+                acc[1] = mma32(fa[1], fb[1], acc[1]);
+                acc[2] = mma32(fa[0], fb[2], acc[2]);
+            }
+            // P[t][i] = exp(l_t - l_i) (C_t . B_i) dt_i, i <= t, for both units, stored
+            // transposed (bf16) for direct fragment reads
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float* Gq = reinterpret_cast<const float*>(smem + Ly::G_OFF) + (2 * (ci & 1) + q) * GR;
+                bf16* Pq = reinterpret_cast<bf16*>(smem + Ly::P_OFF) + q * NPB * BLK;
+                const f32x4 lt0 = lds4f(Gq + CH + 16 * pa0 + 4 * g), lt1 = lds4f(Gq + CH + 16 * pa1 + 4 * g);
+                float li[3], dti[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const int ic = 16 * (i == 0 ? pb0 : i == 1 ? pb1 : pb2) + c16;
+                    li[i] = Gq[CH + ic];
+                    dti[i] = Gq[ic];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    if (i >= nb) break;  // wave-uniform
+                    const int mt = i == 1 ? pa1 : pa0, nt = i == 0 ? pb0 : i == 1 ? pb1 : pb2;
+                    f32x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float e = dti[i] * __expf((i == 1 ? lt1[r] : lt0[r]) - li[i]) * acc[i][r];
+                        v[r] = (mt > nt || c16 <= 4 * g + r) ? e : 0.f;
+                    }
+                    store_tile_tr<SB, false>(Pq + (mt * (mt + 1) / 2 + nt) * BLK, 0, v, g, c16);
+                }
+            }
+        }
+        gates(ci + 1);
+        prefetch_dt(ci + 2);
+        if constexpr (OUT) {
+            lds_barrier();  // output blocks built
+        }
+        prefetch_bc(ci + 1);
+        // X fragments of this wave's rows: lane (g, c) holds X[16kt + 4g + j][row c of the tile]
+        bf16x4 Xf[RT][NTC];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int kt = 0; kt < NTC; ++kt) Xf[rt][kt] = lds4_tr(sX, SX, 16 * kt, 32 * w + 16 * rt, g, c16);
+        if constexpr (OUT) {
+            bf16x4 Pf[NPB];
+#pragma unroll
+            for (int j = 0; j < NPB; ++j) Pf[j] = lds4_tr(sP + j * BLK, SB, 0, 0, g, c16);
+            float el[NTC];
+#pragma unroll
+            for (int mt = 0; mt < NTC; ++mt) el[mt] = G[2 * CH + 16 * mt + c16];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int mt = 0; mt < NTC; ++mt) OT[rt][mt] *= el[mt];
+            // tile mt contracts over token blocks 0..mt, pairs of blocks per product
+#pragma unroll
+            for (int kp = 0; kp < NTC; kp += 2)
+#pragma unroll
+                for (int mt = kp; mt < NTC; ++mt) {
+                    const bool two = mt >= kp + 1;
+                    const int j0 = low_index(mt, kp);
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        OT[rt][mt] = mma32(Xf[rt][kp], two ? Xf[rt][kp + 1] : zero_bf16x4(), Pf[j0],
+                                           two ? Pf[j0 + 1] : zero_bf16x4(), OT[rt][mt]);
+                }
+            // through a resource of the chunk's valid rows: stores past them are dropped
+            const __amdgpu_buffer_rsrc_t ro =
+                make_rsrc(reinterpret_cast<bf16*>(p.out) + c0 * rows_all + r0, (uint32_t)n * x_rb);
+#pragma unroll
+            for (int mt = 0; mt < NTC; ++mt)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    buf_store8(ro, (uint32_t)(16 * mt + c16) * x_rb + 2 * (32 * w + 16 * rt + 4 * g),
+                               to_bf16(OT[rt][mt]));
+        }
+        // S <- exp(l_C) S + B^T diag(d) X: the fp32 operand d * X as hi / lo passes
+        bf16x4 Wh[RT][NTC], Wl[RT][NTC];
+#pragma unroll
+        for (int kt = 0; kt < NTC; kt += 2) {
+            const f32x4 d0 = lds4f(G + 3 * CH + 16 * kt + 4 * g), d1 = lds4f(G + 3 * CH + 16 * kt + 16 + 4 * g);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const Split8 sp = split8_mm(d0 * to_f32(Xf[rt][kt]), d1 * to_f32(Xf[rt][kt + 1]), negI, negIh);
+                Wh[rt][kt] = sp.hi0;
+                Wh[rt][kt + 1] = sp.hi1;
+                Wl[rt][kt] = sp.lo0;
+                Wl[rt][kt + 1] = sp.lo1;
+            }
+        }
+        const float aC = G[4 * CH];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int j = 0; j < NTK; ++j) S[rt][j] = aC * S[rt][j];
+        mgemm_tr_rt<DK, NTK, RT, NTC, false, true>(sB, 0, SK, Wh, Wl, g, c16, S);
+    }
+    if (p.summary && p.M_out && (r0 + 64 * gu) % p.dv == 0 && w >= 2 && lane == 0)
+        p.M_out[int64_t(s) * p.h_v + hg] = lam;
+    if (p.S_final) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int j = 0; j < NTK; ++j)
+                *reinterpret_cast<f32x4*>(p.S_final + (int64_t(s) * rows_all + row(rt)) * DK + 16 * j + 4 * g) =
+                    S[rt][j];
+    }
+}
+
 // Output correction of the sequence-parallel Mamba-2 scan.  With a scalar
 // decay per token the state at token t of piece p is exp(L_t) S_p + (the state
 // of the piece's own tokens from zero), L_t being the log-decay summed from
@@ -608,6 +947,26 @@ static hipError_t launch_ssd_scan_t(const ScanArgs& a, hipStream_t st) {
 
 bool ssd_scan_supported(int dk, int chunk, bool f32io, int dv) {
     return !f32io && chunk == 64 && (dk == 32 || dk == 64 || dk == 128) && dv % 64 == 0;
+}
+
+template <int DK>
+static hipError_t launch_ssd_pair_t(const ScanArgs& a, hipStream_t st) {
+    const size_t lds = SsdPairLds<DK>::BYTES;
+    auto kern = a.out ? ssd_pair_kernel<DK, true> : ssd_pair_kernel<DK, false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n_units), dim3(256), lds, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_ssd_pair(int dk, const ScanArgs& a, hipStream_t st) {
+    switch (dk) {
+        case 32: return launch_ssd_pair_t<32>(a, st);
+        case 64: return launch_ssd_pair_t<64>(a, st);
+        case 128: return launch_ssd_pair_t<128>(a, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_ssd_scan(int dk, const ScanArgs& a, hipStream_t st) {
