@@ -87,6 +87,7 @@ struct ScanArgs {
     int32_t tiles_m;      // row tiles over dk (transition rows), GDN summary only
     int32_t nb;           // B-waves per workgroup (16*nb rows per tile)
     int32_t n_units;
+    int32_t ranked;       // longest segments first (see ranked_segment)
     int32_t wait_limit;   // polls of the solver's bounded wait for the stagers' signals
     // Mamba-2 scan kernel only: with pieces > 1 every segment is cut into that
     // many pieces of whole chunks (the sequence-parallel scan's cut), piece 0
@@ -162,7 +163,7 @@ __device__ __forceinline__ constexpr int low_mt(int j) {
 
 template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1>
 __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(ScanArgs p) {
-    static_assert(RT == 1 || SUMMARY, "several row tiles per wave: block summaries only");
+    static_assert(RT == 1 || (!F32IO && DK >= 32 && CH == 64), "several row tiles per wave: bf16 io, 64-token chunks");
     using Ly = ChunkLds<FAM, DK, CH, F32IO, NB * RT, SUMMARY>;
     constexpr int NTC = CH / 16, NTK = DK / 16;
     constexpr int SK = Ly::SK, SV = Ly::SV, SB = Ly::SB, BLK = Ly::BLK, SLD = Ly::SLD;
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, g = lane >> 4, c16 = lane & 15;
     auto chunk_barrier = []() {
-        if constexpr (SUMMARY) lds_barrier();
+        if constexpr (SUMMARY || RT > 1) lds_barrier();
         else __syncthreads();
     };
     const bool is_b = w < NB;
@@ -202,14 +203,23 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
     const int inner = u % (tiles * hr), outer = u / (tiles * hr);
     const int tile = inner % tiles;
     const int hsub = outer % hpx, o2 = outer / hpx;
-    const int s = o2 % p.n_seq;
+    int s = o2 % p.n_seq;
+    int64_t t0, t1;
+    if (FAM == FAM_GDN && DK == 128 && p.ranked) {
+        const Segment sg = ranked_segment(p.cu, p.n_seq, p.n_tok, s, lane);
+        s = sg.s;
+        t0 = sg.t0;
+        t1 = sg.t1;
+    } else {
+        t0 = p.cu[s];
+        t1 = p.cu[s + 1];
+        t0 = t0 < 0 ? 0 : (t0 > p.n_tok ? p.n_tok : t0);
+        t1 = t1 < t0 ? t0 : (t1 > p.n_tok ? p.n_tok : t1);
+    }
     const int hq = (o2 / p.n_seq) * hpx + hsub;
     const int h = hq * hr + inner / tiles;
     const bool mtile = tile >= p.tiles_b;
     const int row0 = (mtile ? tile - p.tiles_b : tile) * 16 * NB * RT;  // first state row of the tile
-    int64_t t0 = p.cu[s], t1 = p.cu[s + 1];
-    t0 = t0 < 0 ? 0 : (t0 > p.n_tok ? p.n_tok : t0);
-    t1 = t1 < t0 ? t0 : (t1 > p.n_tok ? p.n_tok : t1);
     const int nch = (int)((t1 - t0 + CH - 1) / CH);
     const bool with_out = !SUMMARY && p.out != nullptr;
     const bool load_v = SUMMARY ? !mtile : true;  // transition (M) tiles of a block summary skip V
@@ -432,7 +442,7 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                             if (F32IO) X[rt][mt] += to_f32(lds4_tr(sV(b) + VPL, SV, 16 * mt, col, g, c16));
                         }
                 }
-                if (FAM == FAM_GDN && with_out) {
+                if (FAM == FAM_GDN && RT == 1 && with_out) {
                     // Gated DeltaNet: this chunk's output blocks P, shared by the B-waves
                     // (read after the barrier).  The stagers' second phase is full with
                     // the L blocks; Mamba-2's stagers build P instead.
@@ -486,25 +496,49 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                     }
                 }
             }
-            // Outputs (RT == 1 only) are formed transposed, O^T = S Q^T + U^T P^T:
-            // tile mt holds O[16mt + c16][this wave's rows 4g..4g+3], so each lane
-            // stores 4 consecutive state rows of one token.  S Q^T does not depend
-            // on U: it is formed here, while the B-waves would otherwise wait for
-            // the A-waves at the barrier.
-            f32x4 OT[NTC];
+            // Outputs are formed transposed, O^T = S Q^T + U^T P^T: tile mt holds
+            // O[16mt + c16][row tile's rows 4g..4g+3], so each lane stores 4
+            // consecutive state rows of one token.  S Q^T does not depend on U: it is
+            // formed here, while the B-waves would otherwise wait for the A-waves
+            // at the barrier.
+            f32x4 OT[RT][NTC];
             if (with_out) {
                 const bf16* Qb = sQ(b);
 #pragma unroll
-                for (int mt = 0; mt < NTC; ++mt) OT[mt] = zero4();
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int mt = 0; mt < NTC; ++mt) OT[rt][mt] = zero4();
                 if constexpr (NTK == 1) {
 #pragma unroll
                     for (int mt = 0; mt < NTC; ++mt) {
                         const bf16* qr = Qb + (16 * mt + c16) * SK + 4 * g;
-                        OT[mt] = mma16(Sh[0][0], lds4(qr), OT[mt]);
+                        OT[0][mt] = mma16(Sh[0][0], lds4(qr), OT[0][mt]);
                         if (F32IO) {
-                            OT[mt] = mma16(Sl[0][0], lds4(qr), OT[mt]);
-                            OT[mt] = mma16(Sh[0][0], lds4(qr + KPL), OT[mt]);
+                            OT[0][mt] = mma16(Sl[0][0], lds4(qr), OT[0][mt]);
+                            OT[0][mt] = mma16(Sh[0][0], lds4(qr + KPL), OT[0][mt]);
                         }
+                    }
+                } else if constexpr (RT > 1) {
+                    // two slices of fragments at a time: all of them would not fit
+                    // the registers next to the state
+                    constexpr int NKP = NTK / 2, KB = NKP < 2 ? NKP : 2;
+#pragma unroll
+                    for (int k0 = 0; k0 < NKP; k0 += KB) {
+                        bf16x8 qh[KB][NTC];
+#pragma unroll
+                        for (int kp = 0; kp < KB; ++kp)
+#pragma unroll
+                            for (int mt = 0; mt < NTC; ++mt)
+                                qh[kp][mt] = lds8(Qb + (16 * mt + c16) * SK + 32 * (k0 + kp) + 8 * g);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int kp = 0; kp < KB; ++kp)
+#pragma unroll
+                            for (int mt = 0; mt < NTC; ++mt)
+#pragma unroll
+                                for (int rt = 0; rt < RT; ++rt)
+                                    OT[rt][mt] = mma32(Sh[rt][2 * (k0 + kp)], Sh[rt][2 * (k0 + kp) + 1], qh[kp][mt],
+                                                       OT[rt][mt]);
                     }
                 } else {
                     constexpr int NKP = NTK / 2;
@@ -522,10 +556,10 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                     for (int kp = 0; kp < NKP; ++kp)
 #pragma unroll
                         for (int mt = 0; mt < NTC; ++mt) {
-                            OT[mt] = mma32(Sh[0][2 * kp], Sh[0][2 * kp + 1], qh[kp][mt], OT[mt]);
+                            OT[0][mt] = mma32(Sh[0][2 * kp], Sh[0][2 * kp + 1], qh[kp][mt], OT[0][mt]);
                             if constexpr (F32IO) {
-                                OT[mt] = mma32(Sl[0][2 * kp], Sl[0][2 * kp + 1], qh[kp][mt], OT[mt]);
-                                OT[mt] = mma32(Sh[0][2 * kp], Sh[0][2 * kp + 1], ql[kp][mt], OT[mt]);
+                                OT[0][mt] = mma32(Sl[0][2 * kp], Sl[0][2 * kp + 1], qh[kp][mt], OT[0][mt]);
+                                OT[0][mt] = mma32(Sh[0][2 * kp], Sh[0][2 * kp + 1], ql[kp][mt], OT[0][mt]);
                             }
                         }
                 }
@@ -540,13 +574,14 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                 // output blocks P (transposed fragments), independent of U: requested early
                 constexpr int PPL = (!SUMMARY && F32IO) ? 2 : 1;
                 bf16x4 Pf[PPL][SUMMARY ? 1 : NPB];
-                if (with_out) {
+                auto fetch_p = [&]() {
 #pragma unroll
                     for (int j = 0; j < NPB; ++j)
 #pragma unroll
                         for (int pl = 0; pl < PPL; ++pl)
                             Pf[pl][j] = lds4_tr(sPT(b) + pl * NPB * BLK + j * BLK, SB, 0, 0, g, c16);
-                }
+                };
+                if (with_out && RT == 1) fetch_p();
                 if (FAM == FAM_GDN) {
                     // U = (I + L)^{-1} X over 32-token halves A = blocks {0, 1}, B = {2, 3}:
                     //   U_A = T_A X_A,  U_B = T_B (X_B - L_BA U_A),
@@ -651,16 +686,21 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                         }
                 }
                 if (with_out) {
+                    if (RT > 1) fetch_p();  // not before the substitution: its registers
                     const float coef = (FAM == FAM_GDN) ? p.scale : 1.f;
 #pragma unroll
-                    for (int mt = 0; mt < NTC; ++mt) OT[mt] *= coef * G[2 * CH + 16 * mt + c16];
+                    for (int mt = 0; mt < NTC; ++mt) {
+                        const float cb = coef * G[2 * CH + 16 * mt + c16];
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) OT[rt][mt] *= cb;
+                    }
                     // + U^T P^T: tile mt contracts over token blocks 0..mt, pairs of blocks per MFMA
                     if constexpr (NTC == 1) {
                         const bf16x4 x = Pf[0][0];
-                        OT[0] = mma16(Uh[0][0], x, OT[0]);
+                        OT[0][0] = mma16(Uh[0][0], x, OT[0][0]);
                         if (F32IO) {
-                            OT[0] = mma16(Ul[0][0], x, OT[0]);
-                            OT[0] = mma16(Uh[0][0], Pf[PPL - 1][0], OT[0]);
+                            OT[0][0] = mma16(Ul[0][0], x, OT[0][0]);
+                            OT[0][0] = mma16(Uh[0][0], Pf[PPL - 1][0], OT[0][0]);
                         }
                     } else {
 #pragma unroll
@@ -672,27 +712,36 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                                 const int j0 = low_index(mt, kp);
                                 const bf16x4 x0 = Pf[0][j0];
                                 const bf16x4 x1 = two ? Pf[0][j0 + 1] : zero_bf16x4();
-                                const bf16x4 u1h = two ? Uh[0][kp + 1] : zero_bf16x4();
-                                OT[mt] = mma32(Uh[0][kp], u1h, x0, x1, OT[mt]);
-                                if (F32IO) {
-                                    const bf16x4 u1l = two ? Ul[0][kp + 1] : zero_bf16x4();
-                                    OT[mt] = mma32(Ul[0][kp], u1l, x0, x1, OT[mt]);
-                                    const bf16x4 y0 = Pf[PPL - 1][j0];
-                                    const bf16x4 y1 = two ? Pf[PPL - 1][j0 + 1] : zero_bf16x4();
-                                    OT[mt] = mma32(Uh[0][kp], u1h, y0, y1, OT[mt]);
+#pragma unroll
+                                for (int rt = 0; rt < RT; ++rt) {
+                                    const bf16x4 u1h = two ? Uh[rt][kp + 1] : zero_bf16x4();
+                                    OT[rt][mt] = mma32(Uh[rt][kp], u1h, x0, x1, OT[rt][mt]);
+                                    if (F32IO) {
+                                        const bf16x4 u1l = two ? Ul[rt][kp + 1] : zero_bf16x4();
+                                        OT[rt][mt] = mma32(Ul[rt][kp], u1l, x0, x1, OT[rt][mt]);
+                                        const bf16x4 y0 = Pf[PPL - 1][j0];
+                                        const bf16x4 y1 = two ? Pf[PPL - 1][j0 + 1] : zero_bf16x4();
+                                        OT[rt][mt] = mma32(Uh[rt][kp], u1h, y0, y1, OT[rt][mt]);
+                                    }
                                 }
                             }
                         }
                     }
                     // one 8-byte (bf16) / 16-byte (fp32) store per lane and token tile
-                    const int64_t rowcol = (int64_t)h * p.dv + row0 + 16 * w + 4 * g;
+                    const int64_t rowcol = (int64_t)h * p.dv + row0 + 16 * RT * w + 4 * g;
 #pragma unroll
                     for (int mt = 0; mt < NTC; ++mt) {
                         const int t = 16 * mt + c16;
                         if (t < n) {
                             const int64_t oi = (c0 + t) * p.h_v * (int64_t)p.dv + rowcol;
-                            if (F32IO) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + oi) = OT[mt];
-                            else *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(p.out) + oi) = to_bf16(OT[mt]);
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) {
+                                if (F32IO)
+                                    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + oi + 16 * rt) = OT[rt][mt];
+                                else
+                                    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(p.out) + oi + 16 * rt) =
+                                        to_bf16(OT[rt][mt]);
+                            }
                         }
                     }
                 }
@@ -1118,6 +1167,18 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                     gate_rows(ci + 1);
                 }
                 if (ci + 2 < nch) prefetch(ci + 2);  // a whole chunk of lead time
+                if constexpr (FAM == FAM_GDN && RT > 1) {
+                    // two row tiles per state wave: chunk ci's output blocks
+                    if (with_out) {
+                        using NS = integral_constant<int, NSTG>;
+                        const float* gcp = sG(ci & 1) + 4 * CH;
+                        switch (wa) {
+                            case 0: items(integral_constant<int, 1>(), NS(), P_KIND(), ci & 1, gcp); break;
+                            case 1: items(integral_constant<int, 0>(), NS(), P_KIND(), ci & 1, gcp); break;
+                            default: items(integral_constant<int, 2>(), NS(), P_KIND(), ci & 1, gcp); break;
+                        }
+                    }
+                }
                 chunk_barrier();
                 if (ci + 1 < nch) {
                     a_work(ci + 1);
@@ -1189,10 +1250,10 @@ hipError_t launch_chunk_s(const ScanArgs& a, hipStream_t st) {
         case 2: return launch_chunk_nb<FAM, DK, CH, F32IO, 2, SUMMARY>(a, st);
         case 4: return launch_chunk_nb<FAM, DK, CH, F32IO, 4, SUMMARY>(a, st);
         case 8:
-            // a whole 128-row transition per workgroup: the state-independent work of
-            // a chunk is shared by four state waves of two row tiles each, which
-            // also share every K fragment they read
-            if constexpr (SUMMARY && DK == 128 && CH == 64 && !F32IO)
+            // 128 state rows per workgroup: the state-independent work of a chunk is
+            // shared by four state waves of two row tiles each, which also share
+            // every K (and Q) fragment they read
+            if constexpr ((SUMMARY || FAM == FAM_GDN) && DK == 128 && CH == 64 && !F32IO)
                 return launch_chunk_nb<FAM, DK, CH, F32IO, 4, SUMMARY, 2>(a, st);
             return hipErrorInvalidValue;
     }
@@ -1216,6 +1277,8 @@ size_t chunk_lds_t(int nb, bool summary) {
         case 5: return ChunkLds<FAM, DK, CH, F32IO, 2, true>::BYTES;
         case 8: return ChunkLds<FAM, DK, CH, F32IO, 4, false>::BYTES;
         case 9: return ChunkLds<FAM, DK, CH, F32IO, 4, true>::BYTES;
+        case 16:
+            return (FAM == FAM_GDN && DK == 128 && CH == 64 && !F32IO) ? ChunkLds<FAM, DK, CH, F32IO, 8, false>::BYTES : 0;
         case 17: return (DK == 128 && CH == 64 && !F32IO) ? ChunkLds<FAM, DK, CH, F32IO, 8, true>::BYTES : 0;
     }
     return 0;

@@ -55,11 +55,15 @@ int env_int(const char* name, int dflt) {
 // State-row waves per workgroup for the chunk kernels (16*nb rows per
 // workgroup; every workgroup also runs 4 waves for the state-independent
 // work).  More rows per workgroup share that work; fewer give more workgroups.
-// Pick the largest nb that fits LDS and still fills the 256 CUs.
+// Pick the largest nb that fits LDS and still fills the 256 CUs.  nb = 8 (128 rows:
+// four state waves of two row tiles) takes 4.0 us per chunk where nb = 4 takes 3.2 us
+// for half the rows (dk = 128 scan): one full round of it beats two (16 requests x
+// 32 heads, 512-3072 tokens: 430 -> 290 us; 8 requests of 2048: 218 -> 168 us), while
+// a round it fills only in part loses (6 requests of 512-3072: 131 against 180 us).
 int pick_nw(int fam, int dk, int chunk, bool f32io, int64_t pairs, int rows, int rows2, bool summary) {
     int forced = env_int("LKV_SCAN_NB", 0);
     int fallback = 0;
-    for (int nb = summary ? 8 : 4; nb >= 1; nb >>= 1) {
+    for (int nb = 8; nb >= 1; nb >>= 1) {
         if (rows % (16 * nb) || (rows2 && rows2 % (16 * nb))) continue;
         const size_t lds = scan_lds_bytes(fam, dk, chunk, f32io, nb, summary);
         if (lds == 0 || lds > 160 * 1024) continue;
@@ -67,6 +71,7 @@ int pick_nw(int fam, int dk, int chunk, bool f32io, int64_t pairs, int rows, int
             if (nb == forced) return nb;
             continue;
         }
+        if (nb == 8 && !summary && pairs * (rows / 128) < 240) continue;
         if (!fallback) fallback = nb;
         const int64_t units = pairs * ((rows + (rows2 ? rows2 : 0)) / (16 * nb));
         if (units >= 240) return nb;
@@ -90,6 +95,20 @@ lkv_status check_tokens(const lkv_layer* L, const lkv_tokens* T, bool need_q, bo
     if (L->family == LKV_SSD && T->n_seq > 0 && !T->A) return LKV_E_NULL;
     if (T->n_tok > INT64_C(1) << 40) return LKV_E_SHAPE;
     return LKV_OK;
+}
+
+// Longest segments first, in the kernels of long workgroups (Gated DeltaNet at dk =
+// 128, one workgroup per CU, and ssd_pair_kernel): where workgroups clearly outnumber
+// the CUs (about one round: the order does not matter, and ranking costs 1.5 us), and the segments average ten 64-token
+// chunks or more (16 requests of 512-3072 tokens, 64-row tiles: 416 -> 395 us; fold of 14
+// blocks of 256-2048 tokens: 156 -> 127 us; but 28 blocks of 64-512 tokens: 81 -> 85
+// us, 64 requests of 20-200: 100 -> 120 us).  The Gated DeltaNet unit order gives each
+// XCD every segment only when the q/k heads divide over the 8 XCDs; otherwise an
+// XCD's range would hold the long ones and another's the short ones (4 heads, 10
+// requests: 128 -> 139 us).
+int32_t rank_segments(const lkv_layer* L, const lkv_tokens* T, int64_t units) {
+    return units >= 384 && T->n_seq > 1 && T->n_seq <= RANK_SEGS && T->n_tok >= INT64_C(640) * T->n_seq &&
+           (L->family == LKV_SSD || L->h_qk % 8 == 0);
 }
 
 ScanArgs base_args(const lkv_layer* L, const lkv_tokens* T) {
@@ -120,10 +139,11 @@ ScanArgs base_args(const lkv_layer* L, const lkv_tokens* T) {
 // By `units` of 64 rows (segments x heads x dv / 64):
 //  - pairs once every CU has work without them: from one unit per CU at dk = 128
 //    (16 requests x 64 heads of 64 x 128, 512-3072 tokens: 386 -> 213 us; 288
-//    units of 500-1500 tokens: 103 -> 78 us), from two at smaller dk, where two
-//    of the chunk kernel's workgroups share a CU (dk 64, 1024 units: 131 -> 88 us,
-//    512 units: 68 against 72 us).  With fewer units the serial chain counts, and a
-//    pair's chunk takes longer (64 units: 52 against 86 us).
+//    units of 500-1500 tokens: 103 -> 78 us).  At smaller dk two of the chunk kernel's
+//    workgroups share a CU, so pairs wait until they fill a round of two per CU well
+//    (dk 64, 1024 units: 131 -> 88 us, 2048: 237 -> 170 us; 512 units: 68 against 72
+//    us, 1152: 58 against 61 us).  With fewer units the serial chain counts, and
+//    a pair's chunk takes longer (64 units: 52 against 86 us).
 //  - ssd_scan_kernel at dk = 128 where the chunk kernel would need a second round
 //    of workgroups (they split rows until they fill the CUs, and overshoot) and
 //    one unit per CU does not: 192 units of 1536 tokens 99 -> 62 us, 96 units 32
@@ -136,7 +156,8 @@ SsdKernel ssd_kernel(const lkv_layer* L, int64_t n_seq, bool summary) {
     if (env_int("LKV_SSD_SCAN_KERNEL", 0) == 1) return SSD_SCAN;
     const int64_t per_group = L->dv / 64 * (int64_t)(L->h_v / L->h_qk), units = n_seq * L->h_qk * per_group;
     const int forced = env_int("LKV_SSD_PAIR", -1);
-    if (per_group % 2 == 0 && (forced >= 0 ? forced == 1 : units > (L->dk == 128 ? 256 : 512))) return SSD_PAIR;
+    const bool fills = L->dk == 128 ? units > 256 : (units > 768 && units <= 1024) || units > 1536;
+    if (per_group % 2 == 0 && (forced >= 0 ? forced == 1 : fills)) return SSD_PAIR;
     if (L->dk != 128 || units > 256 || forced >= 0) return SSD_CHUNK;
     const int nb = pick_nw(L->family, L->dk, L->chunk, false, n_seq * L->h_v, L->dv, 0, summary);
     return nb > 0 && units * 4 / nb > 256 ? SSD_SCAN : SSD_CHUNK;
@@ -150,13 +171,14 @@ bool use_ssd_sp(const lkv_layer* L) {
            ssd_scan_supported(L->dk, L->chunk, L->io_dtype == LKV_F32, L->dv);
 }
 
-lkv_status ssd_scan(const lkv_layer* L, SsdKernel kernel, ScanArgs a, hipStream_t st) {
+lkv_status ssd_scan(const lkv_layer* L, const lkv_tokens* T, SsdKernel kernel, ScanArgs a, hipStream_t st) {
     const int64_t units = (int64_t)a.n_seq * L->h_v * (L->dv / 64) / (kernel == SSD_PAIR ? 2 : 1);
     if (units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;
     a.tiles_b = L->dv / 64;
     a.tiles_m = 0;
     a.nb = 4;
     a.n_units = (int32_t)units;
+    a.ranked = rank_segments(L, T, units);
     return hip_status(kernel == SSD_PAIR ? launch_ssd_pair(L->dk, a, st) : launch_ssd_scan(L->dk, a, st));
 }
 
@@ -186,7 +208,7 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     a.S_final = S_final;
     a.summary = 0;
     const SsdKernel sk = ssd_kernel(L, T->n_seq, false);
-    if (sk != SSD_CHUNK) return ssd_scan(L, sk, a, (hipStream_t)stream);
+    if (sk != SSD_CHUNK) return ssd_scan(L, T, sk, a, (hipStream_t)stream);
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, L->dv, 0, false);
     if (nw == 0) return LKV_E_UNSUPPORTED;
     const int64_t units = pairs * (L->dv / (16 * nw));
@@ -195,6 +217,7 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     a.tiles_m = 0;
     a.nb = nw;
     a.n_units = (int32_t)units;
+    a.ranked = rank_segments(L, T, units);
     return hip_status(launch_scan(L, a, (hipStream_t)stream));
 }
 
@@ -495,7 +518,7 @@ lkv_status lkv_block_summary(const lkv_layer* L, const lkv_tokens* T, float* B_o
                                             T->A, M_out, st));
     }
     const SsdKernel sk = ssd_kernel(L, T->n_seq, true);
-    if (sk != SSD_CHUNK) return ssd_scan(L, sk, a, st);
+    if (sk != SSD_CHUNK) return ssd_scan(L, T, sk, a, st);
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, rows_b ? rows_b : rows_m,
                            rows_b ? rows_m : 0, true);
     if (nw == 0) return LKV_E_UNSUPPORTED;
@@ -505,6 +528,7 @@ lkv_status lkv_block_summary(const lkv_layer* L, const lkv_tokens* T, float* B_o
     const int64_t units = pairs * (a.tiles_b + a.tiles_m);
     if (units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;
     a.n_units = (int32_t)units;
+    a.ranked = rank_segments(L, T, units);
     return hip_status(launch_scan(L, a, st));
 }
 

@@ -218,25 +218,42 @@ __device__ __forceinline__ int xcd_unit(int b, int n) {
 
 // The segment with the rank-th most tokens (ties by index), n_seq <= 64: lane j
 // holds segment j's length, and counts the longer ones.  Every wave computes it
-// for itself (about 3 instructions per segment).  Kernels whose workgroups last
-// as long as their segment take the long segments first, so that a ragged
-// batch does not end on a few long ones.
+// for itself, in blocks of 16 segments (a compare and an add each; a taken branch
+// costs as much as a block).  Kernels whose workgroups last as long as their segment
+// take the long segments first, so that a ragged batch does not end on a few
+// long ones.
 constexpr int RANK_SEGS = 64;
-__device__ __forceinline__ int ranked_segment(const int32_t* cu, int n_seq, int64_t n_tok, int rank, int lane) {
-    uint32_t len = 0;
+struct Segment {
+    int s;
+    int64_t t0, t1;  // its tokens, clamped to [0, n_tok]
+};
+__device__ __forceinline__ Segment ranked_segment(const int32_t* cu, int n_seq, int64_t n_tok, int rank, int lane) {
+    uint32_t key = 0;  // lanes past the last segment stay below every segment
+    int32_t a = 0, b = 0;
     if (lane < n_seq) {
         int64_t t0 = cu[lane], t1 = cu[lane + 1];
         t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
         t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-        len = (uint32_t)(t1 - t0) + 1;  // lanes past the last segment: 0, below every segment
+        const int64_t len = t1 - t0 < (1 << 25) ? t1 - t0 : (1 << 25);  // longer ones count as equal
+        key = ((uint32_t)len + 1) * 64 + (63 - lane);
+        a = (int32_t)t0;
+        b = (int32_t)t1;
     }
     int longer = 0;
-    for (int k = 0; k < n_seq; ++k) {
-        const uint32_t lk = (uint32_t)__builtin_amdgcn_readlane((int)len, k);
-        longer += (lk > len || (lk == len && k < lane)) ? 1 : 0;
+    for (int k0 = 0; k0 < n_seq; k0 += 16) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) longer += (uint32_t)__builtin_amdgcn_readlane((int)key, k0 + k) > key ? 1 : 0;
     }
     const uint64_t hit = __ballot(lane < n_seq && longer == rank);
-    return __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
+    const int s = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
+    return Segment{s, __builtin_amdgcn_readlane(a, s), __builtin_amdgcn_readlane(b, s)};
+}
+// Segment s, in the caller's order
+__device__ __forceinline__ Segment plain_segment(const int32_t* cu, int s, int64_t n_tok) {
+    int64_t t0 = cu[s], t1 = cu[s + 1];
+    t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
+    t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
+    return Segment{s, t0, t1};
 }
 
 // Workgroup barrier for LDS traffic: waits for this wave's LDS operations only,

@@ -436,22 +436,17 @@ __global__ __launch_bounds__(256, 2) void ssd_pair_kernel(ScanArgs p) {
     // The pairs of a segment are spread over the XCDs: B and C, which they
     // share, are small next to x and y
     const int n_pairs = p.n_units / p.n_seq;
-    int s = blockIdx.x / n_pairs, pr = blockIdx.x % n_pairs;
-    if (p.n_seq <= RANK_SEGS) {
-        if (p.n_units <= 512 && blockIdx.x >= 256) {
-            const int v = p.n_units - 1 - (blockIdx.x - 256);
-            s = v / n_pairs;
-            pr = v % n_pairs;
-        }
-        s = ranked_segment(p.cu, p.n_seq, p.n_tok, s, lane);
-    }
+    const bool mirrored = p.ranked && p.n_units <= 512 && blockIdx.x >= 256;
+    const int v = mirrored ? p.n_units - 1 - (blockIdx.x - 256) : blockIdx.x;
+    const int pr = v % n_pairs;
+    const Segment sg = p.ranked ? ranked_segment(p.cu, p.n_seq, p.n_tok, v / n_pairs, lane)
+                              : plain_segment(p.cu, v / n_pairs, p.n_tok);
+    const int s = sg.s;
+    const int64_t t0 = sg.t0, t1 = sg.t1;
     const int64_t rows_all = (int64_t)p.h_v * p.dv;
     const int r0 = pr * 128;  // first state row of the pair among the h_v * dv rows
     const int gu = w & 1, hg = (r0 + 64 * gu) / p.dv;  // the unit whose gate rows this wave may form, and its head
     const int hq = (r0 / p.dv) / (p.h_v / p.h_qk);
-    int64_t t0 = p.cu[s], t1 = p.cu[s + 1];
-    t0 = t0 < 0 ? 0 : (t0 > p.n_tok ? p.n_tok : t0);
-    t1 = t1 < t0 ? t0 : (t1 > p.n_tok ? p.n_tok : t1);
     const int nch = (int)((t1 - t0 + CH - 1) / CH);
     const float Ah = p.A[hg];
 

@@ -1,0 +1,101 @@
+"""The Gated DeltaNet scan with 128 state rows per workgroup (two row tiles per
+state wave) against the 64-row form, which computes the same products in the
+same order: bit for bit, on tails, empty and one-token segments, grouped heads,
+pool starts and state-only calls.  And the longest-first order of a ragged
+batch's segments against the segments one at a time."""
+import numpy as np
+import pytest
+
+from paper_2608_11231_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2608_11231_amd import gpu_io, lkv  # noqa: E402
+
+
+def _work(dv, hq, hv, online, seed=11):
+    layer = I.Layer(I.GDN, hq, hv, 128, dv, 64)
+    return I.build_workload("rows", layer, [[] for _ in online], list(online), I.GateLaw(), seed, scale=0.5)
+
+
+def _rand(shape, seed):
+    return 0.5 * torch.randn(shape, device="cuda", generator=torch.Generator("cuda").manual_seed(seed))
+
+
+@pytest.mark.parametrize("dv,hq,hv,online", [(128, 2, 2, (150, 64, 0, 1)), (256, 1, 2, (63, 200)), (512, 1, 1, (129,)),
+                                             (384, 3, 3, (64, 320))])
+def test_128_rows_match_64(dv, hq, hv, online, monkeypatch):
+    w = _work(dv, hq, hv, online)
+    G = gpu_io.GpuWorkload(w, with_cached=False)
+    S0 = _rand(G.S_final.shape, 3)
+    src = torch.tensor([1, -1, 7, 0][:w.n_req], dtype=torch.int32, device="cuda")  # 7: outside the pool
+
+    def passes():
+        res = []
+        for t in (G.out, G.S_final):
+            t.fill_(7.0)
+        G.scan(S0)
+        res += [G.out.clone(), G.S_final.clone()]
+        for pool in (S0, S0.to(torch.bfloat16)):
+            lkv.chunk_scan_from_pool(G.layer, G.online.struct, 0.5, pool, w.n_req, src, G.out, G.S_final)
+            res += [G.out.clone(), G.S_final.clone()]
+        lkv.gdn_chunk_scan(G.layer, G.online.struct, 0.5, S0, None, G.S_final)
+        lkv.gdn_chunk_scan(G.layer, G.online.struct, 0.5, None, G.out, None)
+        res += [G.S_final.clone(), G.out.clone()]
+        torch.cuda.synchronize()
+        return res
+
+    monkeypatch.setenv("LKV_SCAN_NB", "4")
+    ref = passes()
+    monkeypatch.setenv("LKV_SCAN_NB", "8")
+    for i, (a, b) in enumerate(zip(passes(), ref)):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num()), i
+
+
+@pytest.mark.parametrize("fam,n_seq,nb", [(I.GDN, 17, "4"), (I.GDN, 17, "8"), (I.GDN, 64, "8"), (I.GDN, 65, "8"),
+                                          (I.SSD, 17, "4"), (I.SSD, 33, "4")])
+def test_ranked_segments_match_one_at_a_time(fam, n_seq, nb, monkeypatch):
+    monkeypatch.setenv("LKV_SCAN_NB", nb)
+    rng = np.random.default_rng(n_seq)
+    lens = [int(x) for x in rng.integers(300, 1400, n_seq)]
+    lens[3] = lens[5] = 700  # equal lengths keep their order
+    lens[7], lens[11] = 0, 1
+    hv = 16 if n_seq < 60 else 8
+    layer = I.Layer(fam, 2, hv, 128, 128 if fam == I.GDN else 64, 64, "bf16", "bf16" if fam == I.GDN else "f32")
+    n = sum(lens)
+    assert n >= 512 * n_seq
+    g = torch.Generator("cuda").manual_seed(n_seq)
+    unit = lambda x: (x / x.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    q, k = (unit(torch.randn((n, 2, 128), device="cuda", generator=g)) for _ in range(2))
+    v = torch.randn((n, hv, layer.dv), device="cuda", generator=g).to(torch.bfloat16)
+    if fam == I.GDN:
+        gate = (-0.05 * torch.rand((n, hv), device="cuda", generator=g)).to(torch.bfloat16)
+        beta, A = torch.rand((n, hv), device="cuda", generator=g).to(torch.bfloat16), None
+    else:
+        gate, beta = 0.05 * torch.rand((n, hv), device="cuda", generator=g), None
+        A = -1.0 - torch.rand((hv,), device="cuda", generator=g)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    L = gpu_io.layer_struct(layer)
+
+    def scan(a, b):
+        t0, t1 = int(cu[a]), int(cu[b])
+        c = torch.from_numpy(cu[a:b + 1] - cu[a]).cuda()
+        part = [None if x is None else x[t0:t1].contiguous() for x in (q, k, v, gate, beta)]
+        T = lkv.make_tokens(c, t1 - t0, *part, A)
+        out = torch.full((t1 - t0, hv, layer.dv), 7.0, device="cuda", dtype=torch.bfloat16)
+        S = torch.full((b - a, hv, layer.dv, 128), 7.0, device="cuda")
+        if fam == I.GDN:
+            lkv.gdn_chunk_scan(L, T, 0.3, None, out, S)
+        else:
+            lkv.ssd_chunk_scan(L, T, None, out, S)
+        torch.cuda.synchronize()
+        return out, S
+
+    out, S = scan(0, n_seq)
+    for s in range(n_seq):
+        o1, S1 = scan(s, s + 1)
+        assert torch.equal(out[cu[s]:cu[s + 1]], o1) and torch.equal(S[s], S1[0]), s
