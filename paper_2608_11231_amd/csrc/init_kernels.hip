@@ -406,6 +406,171 @@ __global__ __launch_bounds__(64 * NW) void compose_gdn_kernel(ComposeArgs p) {
     for (int nt = 0; nt < NOWN; ++nt) *reinterpret_cast<f32x4*>(dst + 16 * nt) = S[nt];
 }
 
+// The same composition for few (request, head) chains: one 16-row tile per
+// workgroup, DK / 16 waves, wave w forming columns 16w..16w+15 of the new state.
+// A wave needs only its own 16 columns of M, so it stages them for itself (bf16
+// hi / lo in its own part of LDS, transposed reads) ahead of the state it waits
+// for; the waves meet once per step, to exchange the state's hi / lo parts through
+// one of two LDS buffers.  The loads of M and B lead by two steps.  The products of
+// a step are one chain per pass.  Every row tile of a head reads all of M, from
+// L2: with more chains than CUs that traffic is what counts and 64-row workgroups
+// are better.  One 8K request, 32 heads of 128 x 128, 8 blocks (256 workgroups): 24.1 ->
+// 18.0 us, of 32 blocks 79 -> 59 us (1.7 us a step: the LDS round trips of the
+// staged columns and of the exchange, and the split between them).
+template <int DK>
+struct ComposeTileLds {
+    static constexpr int NTK = DK / 16, SM = 20;
+    static constexpr size_t PLANE = size_t(DK) * SM;           // elements of one wave's M columns
+    static constexpr size_t X_OFF = size_t(NTK) * 2 * PLANE * 2;
+    static constexpr size_t X_BUF = size_t(NTK) * 2 * 64 * 8;  // [tile][hi, lo][lane] x 4 bf16
+    static __host__ __device__ constexpr size_t bytes() { return X_OFF + 2 * X_BUF; }
+};
+
+template <int DK, bool BF>
+__global__ __launch_bounds__(64 * (DK / 16), DK == 128 ? 2 : 1) void compose_tile_kernel(ComposeArgs p) {
+    using Ly = ComposeTileLds<DK>;
+    constexpr int NTK = Ly::NTK, SM = Ly::SM, NKP = NTK / 2;
+    static_assert(NTK % 2 == 0, "32-wide slices");
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c16 = lane & 15;
+    bf16* const sMh = reinterpret_cast<bf16*>(smem) + w * 2 * Ly::PLANE;
+    bf16* const sMl = sMh + Ly::PLANE;
+    auto sx = [&](int b, int nt, int pl) {
+        return reinterpret_cast<bf16x4*>(smem + Ly::X_OFF + b * Ly::X_BUF) + (nt * 2 + pl) * 64 + lane;
+    };
+    const bf16x8 negI = neg_eye(g, c16), negIh = neg_eye_hi(g, c16);
+    // units as in compose_gdn_kernel
+    const int u = xcd_unit(blockIdx.x, p.n_units);
+    const int n_req = p.n_units / (p.tiles * p.h_v);
+    const int tile = u % p.tiles;
+    const int r = (u / p.tiles) % n_req;
+    const int h = u / (p.tiles * n_req);
+    const int my_row = tile * 16 + c16;
+    int32_t b0 = p.blk_cu[r], b1 = p.blk_cu[r + 1];
+    b0 = b0 < 0 ? 0 : (b0 > p.n_ids ? p.n_ids : b0);
+    b1 = b1 < b0 ? b0 : (b1 > p.n_ids ? p.n_ids : b1);
+
+    // block ids through the scalar cache; past the request's end or its first
+    // invalid id (position bad_at) the loads re-read the first block
+    typedef __attribute__((address_space(4))) const int32_t const_i32;
+    const const_i32* ids_c = (const const_i32*)p.blk_ids;
+    int32_t bad_at = b1, first = 0;
+    auto id_at = [&](int32_t j) {
+        if (j >= bad_at) return first;
+        const int32_t id = ids_c[j];
+        if (id < 0 || id >= p.n_blk) {
+            bad_at = j;
+            return first;
+        }
+        return id;
+    };
+    f32x4 mreg[2][NTK], breg[2];
+    auto load_m = [&](int32_t id, f32x4 (&m)[NTK]) {
+        const float* Mj = p.M_pool + ((int64_t)id * p.h_v + h) * DK * DK + (lane >> 2) * DK + 16 * w + 4 * (lane & 3);
+#pragma unroll
+        for (int s = 0; s < NTK; ++s) m[s] = *reinterpret_cast<const f32x4*>(Mj + 16 * s * DK);
+    };
+    auto load_b = [&](int32_t id) {
+        return pool4<BF>(p.B_pool, (((int64_t)id * p.h_v + h) * p.dv + my_row) * DK + 16 * w + 4 * g);
+    };
+    const int64_t out_at = (int64_t)my_row * DK + 16 * w + 4 * g;
+    f32x4 S = zero4();
+    if (b0 < b1) first = id_at(b0);
+    if (b0 < bad_at) {
+        S = load_b(first);
+        const int32_t i1 = id_at(b0 + 1);
+        load_m(i1, mreg[0]);
+        breg[0] = load_b(i1);
+        const int32_t i2 = id_at(b0 + 2);
+        load_m(i2, mreg[1]);
+        breg[1] = load_b(i2);
+        int32_t id3 = id_at(b0 + 3);
+        int32_t j = b0;
+        // after block j: publish the state's parts for the next step (buffer j & 1)
+        // and store it where a later step starts from it
+        auto publish = [&](int buf) {
+            const Split4 sp = split4_mm(S, negI);
+            *sx(buf, w, 0) = sp.hi;
+            *sx(buf, w, 1) = sp.lo;
+            if (p.S_steps && j + 1 < b1)
+                *reinterpret_cast<f32x4*>(p.S_steps + (((int64_t)j - r) * p.h_v + h) * p.dv * DK + out_at) = S;
+        };
+        auto step = [&](auto slot_c) {
+            constexpr int SL = decltype(slot_c)::value;
+            // this wave's columns of M_j, in LDS and back as fragments, before the wait
+#pragma unroll
+            for (int s = 0; s < NTK; s += 2) {
+                const Split8 sp = split8_mm(mreg[SL][s], mreg[SL][s + 1], negI, negIh);
+                const int at = (16 * s + (lane >> 2)) * SM + 4 * (lane & 3);
+                *reinterpret_cast<bf16x4*>(sMh + at) = sp.hi0;
+                *reinterpret_cast<bf16x4*>(sMl + at) = sp.lo0;
+                *reinterpret_cast<bf16x4*>(sMh + at + 16 * SM) = sp.hi1;
+                *reinterpret_cast<bf16x4*>(sMl + at + 16 * SM) = sp.lo1;
+            }
+            f32x4 a0 = breg[SL], a1 = zero4(), a2 = zero4();
+            load_m(id3, mreg[SL]);
+            breg[SL] = load_b(id3);
+            id3 = id_at(j + 3);
+            wave_lds_sync();
+            bf16x4 mh[NTK], ml[NTK];
+#pragma unroll
+            for (int s = 0; s < NTK; ++s) {
+                mh[s] = lds4_tr(sMh, SM, 16 * s, 0, g, c16);
+                ml[s] = lds4_tr(sMl, SM, 16 * s, 0, g, c16);
+            }
+            lds_barrier();  // the state after block j - 1 published
+            bf16x4 Sh[NTK], Sl[NTK];
+#pragma unroll
+            for (int s = 0; s < NTK; ++s) {
+                Sh[s] = *sx(SL, s, 0);
+                Sl[s] = *sx(SL, s, 1);
+            }
+#pragma unroll
+            for (int kp = 0; kp < NKP; ++kp) {
+                a0 = mma32(mh[2 * kp], mh[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], a0);
+                a1 = mma32(mh[2 * kp], mh[2 * kp + 1], Sl[2 * kp], Sl[2 * kp + 1], a1);
+                a2 = mma32(ml[2 * kp], ml[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], a2);
+            }
+            S = a0 + (a1 + a2);
+            publish(SL ^ 1);
+        };
+        publish(0);
+        // two steps per round, so that each keeps its registers and buffer; every
+        // wave runs the same number (the block ids are the workgroup's)
+        while (true) {
+            if (++j >= bad_at) break;
+            step(std::integral_constant<int, 0>());
+            if (++j >= bad_at) break;
+            step(std::integral_constant<int, 1>());
+        }
+    }
+    if (bad_at < b1) {
+        const float f = __builtin_nanf("");
+        S = f32x4{f, f, f, f};
+    }
+    *reinterpret_cast<f32x4*>(p.S + ((int64_t)r * p.h_v + h) * p.dv * DK + out_at) = S;
+}
+
+template <int DK>
+static hipError_t launch_compose_tile_t(const ComposeArgs& a, hipStream_t st) {
+    const size_t lds = ComposeTileLds<DK>::bytes();
+    auto kern = a.bf16_pool ? compose_tile_kernel<DK, true> : compose_tile_kernel<DK, false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.n_units), dim3(64 * (DK / 16)), lds, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_compose_tile(int dk, const ComposeArgs& a, hipStream_t st) {
+    switch (dk) {
+        case 64: return launch_compose_tile_t<64>(a, st);
+        case 128: return launch_compose_tile_t<128>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <int DK, int NW>
 static hipError_t launch_compose_gdn_nw(const ComposeArgs& a, hipStream_t st) {
     const size_t lds = ComposeLds<DK>::bytes() + (NW == 8 ? ComposeLds<DK>::xbytes() : 0);

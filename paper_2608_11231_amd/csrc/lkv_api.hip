@@ -301,12 +301,22 @@ lkv_status init_compose(const lkv_layer* L, int32_t n_req, int32_t n_blk, const 
     a.dv = L->dv;
     a.S = S_init;
     a.S_steps = S_steps;
+    // Few chains: one 16-row tile per workgroup (compose_tile_kernel) where those fit
+    // one per CU and the chains are long enough to repay its deeper prologue.  dk =
+    // 128, 256 tiles of 8 blocks: 24 -> 18 us, 512 tiles: 26 against 33 us, 3 blocks:
+    // 12.8 against 14.3 us.  dk = 64: 30 blocks 35 -> 26 us, 8 blocks 13.9 against
+    // 14.5 us.  LKV_COMPOSE_TILE=1 / 0 forces it or the wider form.
+    const int64_t tiles16 = pairs * (L->dv / 16);
+    const int64_t min_blocks = L->dk == 128 ? 4 : 16;
+    const int forced = env_int("LKV_COMPOSE_TILE", -1);
+    const bool tile = (L->dk == 64 || L->dk == 128) &&
+                      (forced >= 0 ? forced == 1 : tiles16 <= 256 && n_ids >= min_blocks * n_req);
     a.nw = nw;
-    a.tiles = L->dv / rows;
+    a.tiles = L->dv / (tile ? 16 : rows);
     const int64_t units = pairs * a.tiles;
     if (units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;
     a.n_units = (int32_t)units;
-    return hip_status(launch_compose_gdn(L->dk, a, st));
+    return hip_status(tile ? launch_compose_tile(L->dk, a, st) : launch_compose_gdn(L->dk, a, st));
 }
 
 // Workspace of the sequence-parallel scan, each region 256-byte aligned:
