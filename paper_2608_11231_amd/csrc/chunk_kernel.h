@@ -169,6 +169,13 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
     constexpr int SK = Ly::SK, SV = Ly::SV, SB = Ly::SB, BLK = Ly::BLK, SLD = Ly::SLD;
     constexpr int NOFF = Ly::NOFF, NPB = Ly::NPB;
     constexpr int KPL = CH * SK, VPL = CH * SV;  // lo-plane offsets (fp32 io)
+    // Gated DeltaNet's output blocks P: the state waves build them in the first
+    // phase, each its share, unless they are few (one wave would build all ten: one
+    // 8K request, 32 heads: 88 -> 72 us with the stagers, two waves 82 -> 79 us) or
+    // already do two row tiles' products there -- then the stagers do.  With four
+    // state waves of one row tile the stagers' first phase is as long as
+    // theirs, and P there is slower (32K scan 224 -> 233 us)
+    constexpr bool P_STAGERS = FAM == FAM_GDN && !SUMMARY && (RT > 1 || NB <= 2);
     extern __shared__ __align__(16) char smem[];
 
     const int tid = threadIdx.x;
@@ -442,7 +449,7 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                             if (F32IO) X[rt][mt] += to_f32(lds4_tr(sV(b) + VPL, SV, 16 * mt, col, g, c16));
                         }
                 }
-                if (FAM == FAM_GDN && RT == 1 && with_out) {
+                if (FAM == FAM_GDN && !P_STAGERS && with_out) {
                     // Gated DeltaNet: this chunk's output blocks P, shared by the B-waves
                     // (read after the barrier).  The stagers' second phase is full with
                     // the L blocks; Mamba-2's stagers build P instead.
@@ -1167,8 +1174,7 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                     gate_rows(ci + 1);
                 }
                 if (ci + 2 < nch) prefetch(ci + 2);  // a whole chunk of lead time
-                if constexpr (FAM == FAM_GDN && RT > 1) {
-                    // two row tiles per state wave: chunk ci's output blocks
+                if constexpr (P_STAGERS) {
                     if (with_out) {
                         using NS = integral_constant<int, NSTG>;
                         const float* gcp = sG(ci & 1) + 4 * CH;
