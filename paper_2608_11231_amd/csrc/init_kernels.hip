@@ -107,12 +107,82 @@ __global__ __launch_bounds__(256) void compose_ssd_kernel(int32_t n_req, int32_t
     }
 }
 
+// The same where a workgroup's elements belong to one (request, head), i.e. the
+// state is a multiple of 256 vectors of 16 pool bytes: block ids and log-decays are
+// then the workgroup's (scalar loads), and four blocks' pool rows are requested at
+// a time.  The element-wise form above waits for an id, a log-decay and a row per
+// block, one after the other.  HBM-bound: 16 requests x 64 heads of 64 x 128, 8 blocks,
+// bf16 pool (201 MB): 61.7 -> 33.3 us (6.0 TB/s).
+template <bool BF>
+__global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, int32_t H, int32_t per_wg,
+                                                               int64_t per_head, const void* __restrict__ B_pool,
+                                                               const float* __restrict__ Lam,
+                                                               const int32_t* __restrict__ ids,
+                                                               const int32_t* __restrict__ blk_cu, int32_t n_ids,
+                                                               float* __restrict__ S, float* __restrict__ S_steps) {
+    constexpr int V = BF ? 2 : 1;  // f32x4 per thread
+    const int32_t rh = blockIdx.x / per_wg;
+    const int64_t e = ((int64_t)(blockIdx.x % per_wg) * 256 + threadIdx.x) * 4 * V;
+    const int32_t r = rh / H, h = rh % H;
+    int32_t b0 = blk_cu[r], b1 = blk_cu[r + 1];
+    b0 = b0 < 0 ? 0 : (b0 > n_ids ? n_ids : b0);
+    b1 = b1 < b0 ? b0 : (b1 > n_ids ? n_ids : b1);
+    f32x4 acc[V] = {};
+    bool bad = false;
+    constexpr int G = 4;
+    for (int32_t j = b0; j < b1 && !bad; j += G) {
+        int32_t id[G];
+        f32x4 b[G][V];
+        float a[G];
+        int m = 0;  // valid blocks of this group
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            id[u] = j + u < b1 ? ids[j + u] : 0;
+            if (m == u && j + u < b1) {
+                if (id[u] >= 0 && id[u] < n_blk) m = u + 1;
+                else bad = true;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            const int32_t row = u < m ? id[u] : (m > 0 ? id[0] : 0);  // a row already being read stands in
+            if (m > 0) {
+                const int64_t at = ((int64_t)row * H + h) * per_head + e;
+#pragma unroll
+                for (int v = 0; v < V; ++v) b[u][v] = pool4<BF>(B_pool, at + 4 * v);
+                a[u] = Lam[(int64_t)row * H + h];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+            if (u >= m) break;
+            const float f = __expf(a[u]);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                acc[v] = j + u == b0 ? b[u][v] : f * acc[v] + b[u][v];
+                if (S_steps && j + u + 1 < b1)
+                    *reinterpret_cast<f32x4*>(S_steps + ((int64_t)(j + u - r) * H + h) * per_head + e + 4 * v) = acc[v];
+            }
+        }
+    }
+    if (bad) {
+        const float f = __builtin_nanf("");
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = f32x4{f, f, f, f};
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) *reinterpret_cast<f32x4*>(S + (int64_t)rh * per_head + e + 4 * v) = acc[v];
+}
+
 // ---------------------------------------------------------------- Mamba-2 block transitions
 // Lambda = A_h * sum_t dt_t over each block (the scalar transition of Eq. 5):
 // a segmented sum over the block's dt rows.  A workgroup covers 64 heads of
 // one block with 16 token lanes (one wave each, so every load is one dt row
-// segment of 256 bytes); each lane keeps several loads in flight, and the 16
-// partial sums are added in a fixed order (reproducible results).
+// segment of 256 bytes); the 16 partial sums are added in a fixed order
+// (reproducible results).  Bound by load latency (a block is a few hundred KB on
+// one CU), so each lane keeps 16 loads in flight, the block's end included: rows
+// past it read as zero through the buffer range.  16 x 8 blocks of 256-2048 tokens, 64
+// heads: 20.9 us with four loads and single ones at the end, 14.7 us.
 constexpr int LAM_LANES = 16;
 __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_t* __restrict__ cu, int32_t n_seq,
                                                                     int64_t n_tok, int32_t H,
@@ -127,16 +197,24 @@ __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_
     int64_t t0 = cu[s], t1 = cu[s + 1];
     t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
     t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (h < H) {
-        int64_t t = t0 + tl;
-        for (; t + 3 * LAM_LANES < t1; t += 4 * LAM_LANES) {
+    constexpr int U = 16;
+    float acc[U] = {};
+    const uint32_t rb = (uint32_t)H * 4;
+    for (int64_t t = t0; t < t1; t += U * LAM_LANES) {  // uniform
+        const int n = (int)(t1 - t < U * LAM_LANES ? t1 - t : U * LAM_LANES);
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dt + t * H), 0, (int)(n * rb), 0x00020000);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] += dt[(t + u * LAM_LANES) * H + h];
+        for (int u = 0; u < U; ++u) {
+            const uint32_t off = h < H ? (uint32_t)(tl + u * LAM_LANES) * rb + (uint32_t)h * 4 : 0xffffffffu;
+            acc[u] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
         }
-        for (; t < t1; t += LAM_LANES) acc[0] += dt[t * H + h];
     }
-    part[tl][hl] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+    for (int m = U / 2; m >= 1; m >>= 1)
+#pragma unroll
+        for (int u = 0; u < m; ++u) acc[u] += acc[u + m];
+    part[tl][hl] = acc[0];
     __syncthreads();
     if (tl == 0 && h < H) {
         float sum = 0.f;
@@ -160,6 +238,13 @@ hipError_t launch_compose_ssd(int32_t n_req, int32_t n_blk, int32_t H, int64_t p
                               int32_t n_ids, float* S, float* S_steps, hipStream_t st) {
     const int64_t total = (int64_t)n_req * H * (per_head / 4);
     if (total == 0) return hipSuccess;
+    const int64_t per_wg = per_head / (bf16_pool ? 2048 : 1024);  // workgroups per (request, head)
+    if (per_head % (bf16_pool ? 2048 : 1024) == 0 && (int64_t)n_req * H * per_wg < (INT64_C(1) << 31)) {
+        auto kern = bf16_pool ? compose_ssd_head_kernel<true> : compose_ssd_head_kernel<false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(n_req * H * per_wg)), dim3(256), 0, st, n_blk, H, (int32_t)per_wg,
+                           per_head, B_pool, Lam, ids, blk_cu, n_ids, S, S_steps);
+        return hipGetLastError();
+    }
     int64_t blocks = (total + 255) / 256;
     if (blocks > 256 * 16) blocks = 256 * 16;
     auto kern = bf16_pool ? compose_ssd_kernel<true> : compose_ssd_kernel<false>;
