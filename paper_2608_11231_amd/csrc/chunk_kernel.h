@@ -25,14 +25,14 @@
 // token x token products and masks, inverses of the 16x16 diagonal blocks of
 // I + L) and the state chain.  The workgroup runs them as a two-stage
 // software pipeline over chunks:
-//   * A-waves (NA = 4).  The stagers (3 for Gated DeltaNet, 4 for Mamba-2)
+//   * A-waves (a_waves).  The stagers (Gated DeltaNet: all but one; Mamba-2: all)
 //     commit chunk c+1 from registers into LDS, form its gate prefix from
 //     their own gate registers and prefetch chunk c+2 from HBM (first phase);
 //     then they build chunk c+1's state-independent blocks, stored pre-split
 //     (bf16 hi/lo) and transposed for direct fragment reads (second phase):
 //     Gated DeltaNet's masked diagonal blocks of L (handed to the solver
 //     through an LDS signal count) and strictly-lower L blocks, or Mamba-2's
-//     output blocks P.  Gated DeltaNet's fourth A-wave, the solver, inverts
+//     output blocks P.  Gated DeltaNet's last A-wave, the solver, inverts
 //     chunk c+1's diagonal blocks (second phase) and combines chunk c's
 //     inverses into the off-diagonal blocks of the two 32x32 diagonal blocks
 //     of (I + L)^{-1} while the B-waves start chunk c (first phase);
@@ -41,8 +41,9 @@
 //     U (32-token halves), the outputs, the state update -- with the fp32
 //     state held in MFMA accumulator registers.
 // LDS holds two pipeline buffers; two workgroup barriers per chunk.  In the
-// block summary the barriers order LDS traffic only (prefetched loads stay in
-// flight across them); the scan keeps full barriers, which measured faster.
+// block summary and the scan of two row tiles per wave the barriers order LDS
+// traffic only (prefetched loads stay in flight across them); the other scans
+// keep full barriers (no slower, and up to 5% faster with fp32 io).
 //
 // Precision: bf16 inputs enter the matrix cores exactly.  fp32 operands of the
 // products that feed the state are split into bf16 hi + lo parts and
@@ -57,7 +58,13 @@
 namespace lkv {
 
 enum { FAM_GDN = 0, FAM_SSD = 1 };
-constexpr int NA = 4;  // A-waves per workgroup
+// A-waves per workgroup: four, but seven in a Gated DeltaNet scan with a single state
+// wave (64-token chunks), whose chunk the three stagers would otherwise bound: the
+// launch leaves room for eight waves per CU, and six stagers halve each one's share
+// of the staging and the token blocks (one 8K request, 32 heads: 72 -> 66 us).
+__host__ __device__ constexpr int a_waves(int fam, int ch, int nb, bool summary) {
+    return fam == FAM_GDN && ch == 64 && nb == 1 && !summary ? 7 : 4;
+}
 // The state waves keep S / e^lam with lam >= -LAM_FLOOR (see gate_rows): the
 // stored state stays within e^32 (about 8e13) of the true one, far from fp32's range.
 constexpr float LAM_FLOOR = 32.f;
@@ -87,7 +94,7 @@ struct ScanArgs {
     int32_t tiles_m;      // row tiles over dk (transition rows), GDN summary only
     int32_t nb;           // B-waves per workgroup (16*nb rows per tile)
     int32_t n_units;
-    int32_t ranked;       // longest segments first (see ranked_segment)
+    int32_t ranked;       // longest segments first (see ranked_segment); Gated DeltaNet: dk 128, 4 state waves
     int32_t wait_limit;   // polls of the solver's bounded wait for the stagers' signals
     // Mamba-2 scan kernel only: with pieces > 1 every segment is cut into that
     // many pieces of whole chunks (the sequence-parallel scan's cut), piece 0
@@ -139,7 +146,7 @@ struct ChunkLds {
     static constexpr size_t TT_OFF = PT_OFF + PT_SZ;
     static constexpr size_t BUF = TT_OFF + TT_SZ;  // one pipeline buffer
     static constexpr size_t GC_OFF = 2 * BUF;      // per A-wave gate prefix
-    static constexpr size_t INV_OFF = GC_OFF + al(NA * 64 * 4);
+    static constexpr size_t INV_OFF = GC_OFF + al(a_waves(FAM, CH, NB, SUMMARY) * 64 * 4);
     static constexpr int INV_BST = 16 * SLD + 4;      // f32 stride of inverse scratch blocks (bank shift)
     // count of stager signals "this chunk's masked diagonal blocks are in LDS"
     static constexpr size_t CNT_OFF = INV_OFF + (HAS_L ? al(size_t(NTC) * INV_BST * 4) : 0);
@@ -161,8 +168,11 @@ __device__ __forceinline__ constexpr int low_mt(int j) {
     return mt;
 }
 
-template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1>
-__global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(ScanArgs p) {
+// RANKED: the longest segments first (see ranked_segment); its own instantiation, as the
+// ranking in the common kernel cost the 32K fold 0.6%
+template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1, bool RANKED = false>
+__global__ __launch_bounds__(64 * (NB + a_waves(FAM, CH, NB, SUMMARY)), (NB + a_waves(FAM, CH, NB, SUMMARY)) / 4)
+void chunk_kernel(ScanArgs p) {
     static_assert(RT == 1 || (!F32IO && DK >= 32 && CH == 64), "several row tiles per wave: bf16 io, 64-token chunks");
     using Ly = ChunkLds<FAM, DK, CH, F32IO, NB * RT, SUMMARY>;
     constexpr int NTC = CH / 16, NTK = DK / 16;
@@ -212,7 +222,7 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
     const int hsub = outer % hpx, o2 = outer / hpx;
     int s = o2 % p.n_seq;
     int64_t t0, t1;
-    if (FAM == FAM_GDN && DK == 128 && p.ranked) {
+    if constexpr (RANKED) {
         const Segment sg = ranked_segment(p.cu, p.n_seq, p.n_tok, s, lane);
         s = sg.s;
         t0 = sg.t0;
@@ -818,9 +828,10 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
         }
     } else {
         // ---- A-waves: HBM -> register prefetch and register -> LDS commit of a chunk
-        // Gated DeltaNet: A-waves 0..NA-2 stage tiles and build the L blocks; A-wave
-        // NA-1 (the solver) builds the triangular inverses.
-        constexpr int NSTG = (FAM == FAM_GDN) ? NA - 1 : NA;
+        // Gated DeltaNet: the A-waves but the last stage tiles and build the L blocks;
+        // the last (the solver) builds the triangular inverses.
+        constexpr int NAW = a_waves(FAM, CH, NB, SUMMARY);
+        constexpr int NSTG = (FAM == FAM_GDN) ? NAW - 1 : NAW;
         const bool stager = wa < NSTG;
         KQTile<CH, DK, F32IO, 64 * NSTG> pk, pq;
         TileRegs<CH, 16 * NB * RT, F32IO, 64 * NSTG> pv;
@@ -1096,6 +1107,18 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
             }
         };
 
+        // f(stager index), the index a compile-time constant in each branch
+        auto by_stager = [&](auto f) {
+            switch (wa) {
+                case 0: f(integral_constant<int, 0>()); break;
+                case 1: f(integral_constant<int, 1>()); break;
+                case 2: f(integral_constant<int, 2>()); break;
+                case 3: if constexpr (NSTG > 3) f(integral_constant<int, 3>()); break;
+                case 4: if constexpr (NSTG > 4) f(integral_constant<int, 4>()); break;
+                default: if constexpr (NSTG > 5) f(integral_constant<int, 5>()); break;
+            }
+        };
+
         // A-waves, second phase: state-independent blocks of chunk ci into buffer ci & 1
         auto a_work = [&](int ci) {
             const int b = ci & 1;
@@ -1112,34 +1135,16 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
             if constexpr (FAM == FAM_GDN) {
                 // stager a masks its diagonal blocks and signals the solver, then
                 // builds the strictly-lower L blocks a, a + NSTG, ...
-                static_assert(NSTG == 3, "three stagers");
-                switch (wa) {
-                    case 0:
-                        diag_prep(integral_constant<int, 2>(), b, gcw);
-                        lds_signal(diag_cnt, lane);
-                        items(integral_constant<int, 0>(), NS(), L_KIND(), b, gcw);
-                        break;
-                    case 1:
-                        diag_prep(integral_constant<int, 1>(), b, gcw);
-                        lds_signal(diag_cnt, lane);
-                        items(integral_constant<int, 1>(), NS(), L_KIND(), b, gcw);
-                        break;
-                    default:
-                        diag_prep(integral_constant<int, 0>(), b, gcw);
-                        lds_signal(diag_cnt, lane);
-                        items(integral_constant<int, 2>(), NS(), L_KIND(), b, gcw);
-                        break;
-                }
+                by_stager([&](auto a_c) {
+                    constexpr int A = decltype(a_c)::value;
+                    diag_prep(integral_constant<int, NSTG - 1 - A>(), b, gcw);
+                    lds_signal(diag_cnt, lane);
+                    items(a_c, NS(), L_KIND(), b, gcw);
+                });
             } else if (with_out) {
                 // Mamba-2: stager a builds the output blocks P a, a + NSTG, ... (these
                 // waves are otherwise idle in this phase)
-                static_assert(NSTG == 4, "four stagers");
-                switch (wa) {
-                    case 0: items(integral_constant<int, 0>(), NS(), P_KIND(), b, gcw); break;
-                    case 1: items(integral_constant<int, 1>(), NS(), P_KIND(), b, gcw); break;
-                    case 2: items(integral_constant<int, 2>(), NS(), P_KIND(), b, gcw); break;
-                    default: items(integral_constant<int, 3>(), NS(), P_KIND(), b, gcw); break;
-                }
+                by_stager([&](auto a_c) { items(a_c, NS(), P_KIND(), b, gcw); });
             }
         };
 
@@ -1175,14 +1180,16 @@ __global__ __launch_bounds__(64 * (NB + NA), (NB + NA) / 4) void chunk_kernel(Sc
                 }
                 if (ci + 2 < nch) prefetch(ci + 2);  // a whole chunk of lead time
                 if constexpr (P_STAGERS) {
+                    // chunk ci's output blocks, the larger shares away from stager 0
+                    // (the gate rows)
                     if (with_out) {
-                        using NS = integral_constant<int, NSTG>;
                         const float* gcp = sG(ci & 1) + 4 * CH;
-                        switch (wa) {
-                            case 0: items(integral_constant<int, 1>(), NS(), P_KIND(), ci & 1, gcp); break;
-                            case 1: items(integral_constant<int, 0>(), NS(), P_KIND(), ci & 1, gcp); break;
-                            default: items(integral_constant<int, 2>(), NS(), P_KIND(), ci & 1, gcp); break;
-                        }
+                        by_stager([&](auto a_c) {
+                            constexpr int A = decltype(a_c)::value;
+                            constexpr int SLOT = NSTG == 3 ? (A == 0 ? 1 : (A == 1 ? 0 : 2)) : NSTG - 1 - A;
+                            items(integral_constant<int, SLOT>(), integral_constant<int, NSTG>(), P_KIND(), ci & 1,
+                                  gcp);
+                        });
                     }
                 }
                 chunk_barrier();
@@ -1242,10 +1249,12 @@ template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1>
 hipError_t launch_chunk_nb(const ScanArgs& a, hipStream_t st) {
     const size_t lds = ChunkLds<FAM, DK, CH, F32IO, NB * RT, SUMMARY>::BYTES;
     auto kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT>;
+    if constexpr (FAM == FAM_GDN && DK == 128 && CH == 64 && NB == 4)
+        if (a.ranked) kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT, true>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(a.n_units), dim3(64 * (NB + NA)), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(a.n_units), dim3(64 * (NB + a_waves(FAM, CH, NB, SUMMARY))), lds, st, a);
     return hipGetLastError();
 }
 
