@@ -180,9 +180,9 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
 // one block with 16 token lanes (one wave each, so every load is one dt row
 // segment of 256 bytes); the 16 partial sums are added in a fixed order
 // (reproducible results).  Bound by load latency (a block is a few hundred KB on
-// one CU), so each lane keeps 16 loads in flight, the block's end included: rows
+// one CU), so each lane keeps eight loads in flight, the block's end included: rows
 // past it read as zero through the buffer range.  16 x 8 blocks of 256-2048 tokens, 64
-// heads: 20.9 us with four loads and single ones at the end, 14.7 us.
+// heads: 20.9 us with four loads and single ones at the end, 13.9 us.
 constexpr int LAM_LANES = 16;
 __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_t* __restrict__ cu, int32_t n_seq,
                                                                     int64_t n_tok, int32_t H,
@@ -197,17 +197,19 @@ __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_
     int64_t t0 = cu[s], t1 = cu[s + 1];
     t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
     t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-    constexpr int U = 16;
+    constexpr int U = 8;
     float acc[U] = {};
     const uint32_t rb = (uint32_t)H * 4;
-    for (int64_t t = t0; t < t1; t += U * LAM_LANES) {  // uniform
-        const int n = (int)(t1 - t < U * LAM_LANES ? t1 - t : U * LAM_LANES);
-        const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dt + t * H), 0, (int)(n * rb), 0x00020000);
+    if (h < H) {  // not lanes past the heads with out-of-range offsets: those loads are slow
+        for (int64_t t = t0; t < t1; t += U * LAM_LANES) {
+            const int n = (int)(t1 - t < U * LAM_LANES ? t1 - t : U * LAM_LANES);
+            const __amdgpu_buffer_rsrc_t r =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dt + t * H), 0, (int)(n * rb), 0x00020000);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t off = h < H ? (uint32_t)(tl + u * LAM_LANES) * rb + (uint32_t)h * 4 : 0xffffffffu;
-            acc[u] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+            for (int u = 0; u < U; ++u) {
+                const uint32_t off = (uint32_t)(tl + u * LAM_LANES) * rb + (uint32_t)h * 4;
+                acc[u] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+            }
         }
     }
 #pragma unroll
