@@ -411,11 +411,16 @@ lkv_status chunk_scan_sp(const lkv_layer* L, const lkv_tokens* T, float scale, c
         c.y = out;
         c.S_final = S_final;
         c.tiles = tiles;
-        // chunk slots: about one workgroup per CU, at most a piece's chunks
-        // (ceil(ceil(n_tok / P) / CH) bounds them) and at most 8
+        // chunk slots: at most one workgroup per CU in all (a second one of a CU
+        // composes the same start states again: 24 heads in 8 pieces 52 -> 46 us with one
+        // slot instead of two, in 4 pieces 39 -> 34 us with three instead of four) unless a
+        // lone slot's chain of chunks gets long (50 heads, 16 chunks a piece: two slots
+        // 79, one 83 us); at most a piece's chunks (ceil(ceil(n_tok / P) / CH) bounds
+        // them) and at most 8
         const int64_t max_chunks = ((T->n_tok + pieces - 1) / pieces + L->chunk - 1) / L->chunk;
         const int64_t base = (int64_t)n_req * (pieces - 1) * L->h_v * tiles;
-        int64_t slots = (256 + base - 1) / base;
+        int64_t slots = 256 / base;
+        if (slots < 2 && max_chunks > 8) slots = (256 + base - 1) / base;
         if (slots > max_chunks) slots = max_chunks;
         if (env_int("LKV_SSD_CORRECT_SLOTS", 0) > 0) slots = env_int("LKV_SSD_CORRECT_SLOTS", 0);
         c.slots = (int32_t)(slots < 1 ? 1 : (slots > 8 ? 8 : slots));
