@@ -25,7 +25,7 @@ hipError_t launch_compose_ssd(int32_t n_req, int32_t n_blk, int32_t H, int64_t p
                               bool bf16_pool, const float* Lam, const int32_t* ids, const int32_t* blk_cu,
                               int32_t n_ids, float* S, float* S_steps, hipStream_t st);
 hipError_t launch_compose_gdn(int dk, const ComposeArgs& a, hipStream_t st);
-// one 16-row tile per workgroup, for few chains (dk 64 or 128)
+// one 16-row tile per workgroup, for few chains (dk 64 or 128); the same bits
 hipError_t launch_compose_tile(int dk, const ComposeArgs& a, hipStream_t st);
 hipError_t launch_ssd_lambda(const int32_t* cu, int32_t n_seq, int64_t n_tok, int32_t H, const float* dt,
                              const float* A, float* Lam, hipStream_t st);

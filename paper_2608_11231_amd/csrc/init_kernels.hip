@@ -595,7 +595,7 @@ __global__ __launch_bounds__(64 * (DK / 16), DK == 128 ? 2 : 1) void compose_til
                 *reinterpret_cast<bf16x4*>(sMh + at + 16 * SM) = sp.hi1;
                 *reinterpret_cast<bf16x4*>(sMl + at + 16 * SM) = sp.lo1;
             }
-            f32x4 a0 = breg[SL], a1 = zero4(), a2 = zero4();
+            f32x4 acc = breg[SL];
             load_m(id3, mreg[SL]);
             breg[SL] = load_b(id3);
             id3 = id_at(j + 3);
@@ -615,11 +615,11 @@ __global__ __launch_bounds__(64 * (DK / 16), DK == 128 ? 2 : 1) void compose_til
             }
 #pragma unroll
             for (int kp = 0; kp < NKP; ++kp) {
-                a0 = mma32(mh[2 * kp], mh[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], a0);
-                a1 = mma32(mh[2 * kp], mh[2 * kp + 1], Sl[2 * kp], Sl[2 * kp + 1], a1);
-                a2 = mma32(ml[2 * kp], ml[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], a2);
+                acc = mma32(mh[2 * kp], mh[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], acc);
+                acc = mma32(mh[2 * kp], mh[2 * kp + 1], Sl[2 * kp], Sl[2 * kp + 1], acc);
+                acc = mma32(ml[2 * kp], ml[2 * kp + 1], Sh[2 * kp], Sh[2 * kp + 1], acc);
             }
-            S = a0 + (a1 + a2);
+            S = acc;
             publish(SL ^ 1);
         };
         publish(0);

@@ -303,7 +303,7 @@ lkv_status init_compose(const lkv_layer* L, int32_t n_req, int32_t n_blk, const 
     a.S_steps = S_steps;
     // Few chains: one 16-row tile per workgroup (compose_tile_kernel) where those fit
     // one per CU and the chains are long enough to repay its deeper prologue.  dk =
-    // 128, 256 tiles of 8 blocks: 24 -> 18 us, 512 tiles: 26 against 33 us, 3 blocks:
+    // 128, 256 tiles of 8 blocks: 22 -> 15 us, 512 tiles: 26 against 33 us, 3 blocks:
     // 12.8 against 14.3 us.  dk = 64: 30 blocks 35 -> 26 us, 8 blocks 13.9 against
     // 14.5 us.  LKV_COMPOSE_TILE=1 / 0 forces it or the wider form.
     const int64_t tiles16 = pairs * (L->dv / 16);

@@ -56,3 +56,49 @@ def test_tiles_match_fp64(dk, dv, h, bf16, monkeypatch):
         # 16 significant bits per split operand, a contraction per step: the state bar, 1e-4
         for got in (S, S64):
             assert (got[r].double() - ref).abs().max() <= 1e-4 * ref.abs().max().clamp(min=1e-30), (r, len(x))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("dk,dv", [(128, 64), (64, 128)])
+def test_tiles_keep_the_wide_forms_bits(dk, dv, bf16, monkeypatch):
+    """Same split products in the same order in both forms: which one the sizes choose must not show."""
+    g = torch.Generator("cuda").manual_seed(dk + dv)
+    n_blk, h, Ks = 12, 3, [1, 2, 3, 8, 17]
+    B = torch.randn((n_blk, h, dv, dk), device="cuda", generator=g)
+    B = B.to(torch.bfloat16) if bf16 else B
+    M = 0.9 / dk ** 0.5 * torch.randn((n_blk, h, dk, dk), device="cuda", generator=g)
+    ids = torch.randint(0, n_blk, (sum(Ks),), device="cuda", generator=g).to(torch.int32)
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum(Ks)]).astype(np.int32)).cuda()
+    L = lkv.make_layer(lkv.GDN, h, h, dk, dv, 64)
+    got = []
+    for tile in "01":
+        monkeypatch.setenv("LKV_COMPOSE_TILE", tile)
+        S = torch.full((len(Ks), h, dv, dk), 7.0, device="cuda")
+        (lkv.init_compose_bf16 if bf16 else lkv.init_compose)(L, n_blk, B, M, ids, cu, sum(Ks), S)
+        got.append(S)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
+
+
+def test_sequence_parallel_scan_keeps_bits(monkeypatch):
+    """The pieces' start states are the composition's running states: outputs alike in both forms."""
+    g = torch.Generator("cuda").manual_seed(9)
+    n, h, d = 700, 2, 128
+    unit = lambda x: (x / x.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    q, k = (unit(torch.randn((n, h, d), device="cuda", generator=g)) for _ in range(2))
+    v = torch.randn((n, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    gate = (-0.05 * torch.rand((n, h), device="cuda", generator=g)).to(torch.bfloat16)
+    beta = torch.rand((n, h), device="cuda", generator=g).to(torch.bfloat16)
+    S0 = torch.randn((2, h, d, d), device="cuda", generator=g)
+    L = lkv.make_layer(lkv.GDN, h, h, d, d, 64)
+    T = lkv.make_tokens(torch.tensor([0, 500, n], dtype=torch.int32, device="cuda"), n, q, k, v, gate, beta)
+    ws = torch.empty(lkv.chunk_scan_sp_workspace(L, 2, 4), dtype=torch.uint8, device="cuda")
+    got = []
+    for tile in "01":
+        monkeypatch.setenv("LKV_COMPOSE_TILE", tile)
+        out, S = torch.full_like(v, 7.0), torch.full_like(S0, 7.0)
+        lkv.chunk_scan_sp(L, T, 0.09, S0, out, S, 4, ws)
+        got.append((out, S))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+    assert torch.equal(got[0][1].view(torch.int32), got[1][1].view(torch.int32))
