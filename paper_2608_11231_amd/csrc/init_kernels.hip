@@ -181,9 +181,12 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
 // segment of 256 bytes); the 16 partial sums are added in a fixed order
 // (reproducible results).  Bound by load latency (a block is a few hundred KB on
 // one CU), so each lane keeps eight loads in flight, the block's end included: rows
-// past it read as zero through the buffer range.  16 x 8 blocks of 256-2048 tokens, 64
-// heads: 20.9 us with four loads and single ones at the end, 13.9 us.
+// past it read as zero through the buffer range (WIDE: eight rows of a lane span more
+// than 32-bit offsets, so plain loads, each behind a branch).  16 x 8 blocks of 256-2048
+// tokens, 64 heads: 20.9 us with four loads and single ones at the end, 13.9 us.
 constexpr int LAM_LANES = 16;
+constexpr int LAM_U = 8;  // loads in flight per lane
+template <bool WIDE>
 __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_t* __restrict__ cu, int32_t n_seq,
                                                                     int64_t n_tok, int32_t H,
                                                                     const float* __restrict__ dt,
@@ -192,31 +195,58 @@ __global__ __launch_bounds__(64 * LAM_LANES) void ssd_lambda_kernel(const int32_
     __shared__ float part[LAM_LANES][64];
     const int hg = blockIdx.x % ((H + 63) / 64);
     const int s = blockIdx.x / ((H + 63) / 64);
-    const int tl = threadIdx.x >> 6, hl = threadIdx.x & 63;
+    const int tl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hl = threadIdx.x & 63;
     const int h = hg * 64 + hl;
     int64_t t0 = cu[s], t1 = cu[s + 1];
     t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
     t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-    constexpr int U = 8;
-    float acc[U] = {};
+    constexpr int U = LAM_U;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     const uint32_t rb = (uint32_t)H * 4;
-    if (h < H) {  // not lanes past the heads with out-of-range offsets: those loads are slow
-        for (int64_t t = t0; t < t1; t += U * LAM_LANES) {
-            const int n = (int)(t1 - t < U * LAM_LANES ? t1 - t : U * LAM_LANES);
-            const __amdgpu_buffer_rsrc_t r =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dt + t * H), 0, (int)(n * rb), 0x00020000);
+    if (h < H && t0 + tl < t1) {  // not lanes past the heads with out-of-range offsets: those loads are slow
+        // this wave's rows are t0 + tl + LAM_LANES * k, k < K: those of whole groups of four
+        // go to the four sums in turn, the last few to the first
+        static_assert(U == 8, "two groups per pass");
+        const int64_t K = (t1 - t0 - tl + LAM_LANES - 1) / LAM_LANES, K4 = K & ~INT64_C(3);
+        int64_t k = 0;
+        float x[U];
+        auto load = [&]() {  // rows k .. k + U - 1
+            const int64_t t = t0 + k * LAM_LANES;
+            if constexpr (WIDE) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t off = (uint32_t)(tl + u * LAM_LANES) * rb + (uint32_t)h * 4;
-                acc[u] += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+                for (int u = 0; u < U; ++u) x[u] = k + u < K ? dt[(t + tl + u * LAM_LANES) * H + h] : 0.f;
+            } else {
+                const int n = (int)(t1 - t < U * LAM_LANES ? t1 - t : U * LAM_LANES);
+                const __amdgpu_buffer_rsrc_t r =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dt + t * H), 0, (int)(n * rb), 0x00020000);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t off = (uint32_t)(tl + u * LAM_LANES) * rb + (uint32_t)h * 4;
+                    x[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+                }
             }
+        };
+        for (; k + U <= K4; k += U) {
+            load();
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc[u % 4] += x[u];
+        }
+        if (k < K) {
+            // at most one whole group and three more rows; adding the zeros past them changes
+            // nothing (no sum is -0), and a branch each would cost as much as the loads
+            load();
+            const bool group = k < K4;
+            acc[0] += x[0];
+#pragma unroll
+            for (int u = 1; u < 4; ++u) {
+                acc[u] += group ? x[u] : 0.f;
+                acc[0] += group ? 0.f : x[u];
+            }
+#pragma unroll
+            for (int u = 4; u < U - 1; ++u) acc[0] += x[u];
         }
     }
-#pragma unroll
-    for (int m = U / 2; m >= 1; m >>= 1)
-#pragma unroll
-        for (int u = 0; u < m; ++u) acc[u] += acc[u + m];
-    part[tl][hl] = acc[0];
+    part[tl][hl] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     __syncthreads();
     if (tl == 0 && h < H) {
         float sum = 0.f;
@@ -230,8 +260,10 @@ hipError_t launch_ssd_lambda(const int32_t* cu, int32_t n_seq, int64_t n_tok, in
                              const float* A, float* Lam, hipStream_t st) {
     const int64_t grid = (int64_t)n_seq * ((H + 63) / 64);
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL(ssd_lambda_kernel, dim3((unsigned)grid), dim3(64 * LAM_LANES), 0, st, cu, n_seq, n_tok, H, dt,
-                       A, Lam);
+    // a pass's rows in one buffer range of less than 2^32 bytes
+    const bool wide = (int64_t)H * 4 * LAM_U * LAM_LANES >= (INT64_C(1) << 32);
+    hipLaunchKernelGGL(wide ? ssd_lambda_kernel<true> : ssd_lambda_kernel<false>, dim3((unsigned)grid),
+                       dim3(64 * LAM_LANES), 0, st, cu, n_seq, n_tok, H, dt, A, Lam);
     return hipGetLastError();
 }
 

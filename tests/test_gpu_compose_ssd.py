@@ -67,3 +67,46 @@ def test_lambda_matches_fp64(h):
         ref = A.double() * dt[cu[s]:cu[s + 1]].double().sum(0)
         # a sum of at most 700 fp32 terms of one sign over 256 partial sums
         assert ((M[s].double() - ref).abs() <= 4e-6 * ref.abs() + 1e-30).all(), s
+
+
+def _fold_order(x):
+    """The fold's fp32 sum of one block's rows [n, h]: 16 token lanes, each with four sums over
+    whole groups of four of its rows and the rest on the first, lanes added in order."""
+    x = x.astype(np.float32)
+    total = np.zeros(x.shape[1], np.float32)
+    for lane in range(16):
+        rows = x[lane::16]
+        acc, full = np.zeros((4, x.shape[1]), np.float32), len(rows) // 4 * 4
+        for k, r in enumerate(rows):
+            acc[k % 4 if k < full else 0] += r
+        total += (acc[0] + acc[1]) + (acc[2] + acc[3])
+    return total
+
+
+@pytest.mark.parametrize("h", [1, 8, 65])
+def test_lambda_order_of_the_sum(h):
+    """Every remainder of the fold's loops (eight rows of a lane, then four, then single ones), bit for bit."""
+    lens = [*range(0, 40), 127, 128, 129, 191, 192, 193, 255, 257, 319, 320, 450, 1000]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rng = np.random.default_rng(h)
+    dt = rng.uniform(0, 0.2, (int(cu[-1]), h)).astype(np.float32)
+    A = -rng.uniform(1, 16, h).astype(np.float32)
+    L = lkv.make_layer(lkv.SSD, 1, h, 64, 64, 64, torch.bfloat16, torch.float32)
+    M = torch.full((len(lens), h), 7.0, device="cuda")
+    T = lkv.make_tokens(torch.from_numpy(cu).cuda(), int(cu[-1]), None, None, None, torch.from_numpy(dt).cuda(), None,
+                        torch.from_numpy(A).cuda())
+    lkv.block_summary(L, T, None, M)
+    ref = np.stack([A * _fold_order(dt[cu[s]:cu[s + 1]]) for s in range(len(lens))])
+    assert np.array_equal(M.cpu().numpy(), ref)
+
+
+def test_lambda_rows_past_32_bit_offsets():
+    """128 dt rows of 2^23 heads are 2^32 bytes: eight rows of a lane span more than 32-bit offsets hold."""
+    h, n = 1 << 23, 130
+    dt = (torch.arange(n, device="cuda") % 8 / 8.0).to(torch.float32)[:, None].expand(n, h).contiguous()
+    A = torch.full((h,), -2.0, device="cuda")
+    L = lkv.make_layer(lkv.SSD, 1, h, 16, 16, 16, torch.bfloat16, torch.float32)
+    M = torch.full((1, h), 7.0, device="cuda")
+    cu = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    lkv.block_summary(L, lkv.make_tokens(cu, n, None, None, None, dt, None, A), None, M)
+    assert bool((M == -2.0 * float((np.arange(n) % 8 / 8.0).sum())).all())
