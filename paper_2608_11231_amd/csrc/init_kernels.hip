@@ -108,11 +108,15 @@ __global__ __launch_bounds__(256) void compose_ssd_kernel(int32_t n_req, int32_t
 }
 
 // The same where a workgroup's elements belong to one (request, head), i.e. the
-// state is a multiple of 256 vectors of 16 pool bytes: block ids and log-decays are
-// then the workgroup's (scalar loads), and four blocks' pool rows are requested at
-// a time.  The element-wise form above waits for an id, a log-decay and a row per
-// block, one after the other.  HBM-bound: 16 requests x 64 heads of 64 x 128, 8 blocks,
-// bf16 pool (201 MB): 61.7 -> 33.3 us (6.0 TB/s).
+// state is a multiple of SSD_HEAD_ELEMS: block ids and log-decays are then the workgroup's
+// (scalar loads), and up to four blocks' pool rows are requested at a time, only those
+// that are there (a stand-in for a missing one is read like any other: requests of one
+// block took 21.8 us with them, 12.9 us without, 15.1 us element-wise; 16 requests x 64
+// heads of 64 x 128, fp32).  The element-wise form above waits for an id, a log-decay and a row per
+// block, one after the other.  HBM-bound: 16 requests x 64 heads of 64 x 128, 8 blocks
+// each out of 64, bf16 pool 58.6 -> 26.8 us, fp32 pool (302 MB): 58.1 -> 44.2 us (with one
+// vector per thread 46.0, with a thread's two side by side 55.1).
+constexpr int SSD_HEAD_ELEMS = 2048;  // state elements of a workgroup
 template <bool BF>
 __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, int32_t H, int32_t per_wg,
                                                                int64_t per_head, const void* __restrict__ B_pool,
@@ -120,9 +124,11 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
                                                                const int32_t* __restrict__ ids,
                                                                const int32_t* __restrict__ blk_cu, int32_t n_ids,
                                                                float* __restrict__ S, float* __restrict__ S_steps) {
-    constexpr int V = BF ? 2 : 1;  // f32x4 per thread
+    constexpr int V = SSD_HEAD_ELEMS / 1024;  // f32x4 per thread
     const int32_t rh = blockIdx.x / per_wg;
-    const int64_t e = ((int64_t)(blockIdx.x % per_wg) * 256 + threadIdx.x) * 4 * V;
+    // a thread's vectors: 16 pool bytes side by side (bf16), or one of each half (fp32)
+    constexpr int VS = BF ? 4 : 1024;
+    const int64_t e = (int64_t)(blockIdx.x % per_wg) * SSD_HEAD_ELEMS + threadIdx.x * (BF ? 4 * V : 4);
     const int32_t r = rh / H, h = rh % H;
     int32_t b0 = blk_cu[r], b1 = blk_cu[r + 1];
     b0 = b0 < 0 ? 0 : (b0 > n_ids ? n_ids : b0);
@@ -145,13 +151,11 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
         }
 #pragma unroll
         for (int u = 0; u < G; ++u) {
-            const int32_t row = u < m ? id[u] : (m > 0 ? id[0] : 0);  // a row already being read stands in
-            if (m > 0) {
-                const int64_t at = ((int64_t)row * H + h) * per_head + e;
+            if (u >= m) break;  // wave-uniform; no stand-in rows: short requests would read theirs four times
+            const int64_t at = ((int64_t)id[u] * H + h) * per_head + e;
 #pragma unroll
-                for (int v = 0; v < V; ++v) b[u][v] = pool4<BF>(B_pool, at + 4 * v);
-                a[u] = Lam[(int64_t)row * H + h];
-            }
+            for (int v = 0; v < V; ++v) b[u][v] = pool4<BF>(B_pool, at + VS * v);
+            a[u] = Lam[(int64_t)id[u] * H + h];
         }
 #pragma unroll
         for (int u = 0; u < G; ++u) {
@@ -161,7 +165,7 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
             for (int v = 0; v < V; ++v) {
                 acc[v] = j + u == b0 ? b[u][v] : f * acc[v] + b[u][v];
                 if (S_steps && j + u + 1 < b1)
-                    *reinterpret_cast<f32x4*>(S_steps + ((int64_t)(j + u - r) * H + h) * per_head + e + 4 * v) = acc[v];
+                    *reinterpret_cast<f32x4*>(S_steps + ((int64_t)(j + u - r) * H + h) * per_head + e + VS * v) = acc[v];
             }
         }
     }
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(256) void compose_ssd_head_kernel(int32_t n_blk, in
         for (int v = 0; v < V; ++v) acc[v] = f32x4{f, f, f, f};
     }
 #pragma unroll
-    for (int v = 0; v < V; ++v) *reinterpret_cast<f32x4*>(S + (int64_t)rh * per_head + e + 4 * v) = acc[v];
+    for (int v = 0; v < V; ++v) *reinterpret_cast<f32x4*>(S + (int64_t)rh * per_head + e + VS * v) = acc[v];
 }
 
 // ---------------------------------------------------------------- Mamba-2 block transitions
@@ -272,8 +276,8 @@ hipError_t launch_compose_ssd(int32_t n_req, int32_t n_blk, int32_t H, int64_t p
                               int32_t n_ids, float* S, float* S_steps, hipStream_t st) {
     const int64_t total = (int64_t)n_req * H * (per_head / 4);
     if (total == 0) return hipSuccess;
-    const int64_t per_wg = per_head / (bf16_pool ? 2048 : 1024);  // workgroups per (request, head)
-    if (per_head % (bf16_pool ? 2048 : 1024) == 0 && (int64_t)n_req * H * per_wg < (INT64_C(1) << 31)) {
+    const int64_t per_wg = per_head / SSD_HEAD_ELEMS;  // workgroups per (request, head)
+    if (per_head % SSD_HEAD_ELEMS == 0 && (int64_t)n_req * H * per_wg < (INT64_C(1) << 31)) {
         auto kern = bf16_pool ? compose_ssd_head_kernel<true> : compose_ssd_head_kernel<false>;
         hipLaunchKernelGGL(kern, dim3((unsigned)(n_req * H * per_wg)), dim3(256), 0, st, n_blk, H, (int32_t)per_wg,
                            per_head, B_pool, Lam, ids, blk_cu, n_ids, S, S_steps);

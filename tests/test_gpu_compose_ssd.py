@@ -16,7 +16,7 @@ from paper_2608_11231_amd import lkv  # noqa: E402
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("dk,dv,h", [(128, 64, 3), (16, 64, 2), (64, 16, 5), (32, 48, 1)])
+@pytest.mark.parametrize("dk,dv,h", [(128, 64, 3), (16, 64, 2), (64, 16, 5), (32, 48, 1), (32, 64, 2)])
 def test_compose_matches_fp64(dk, dv, h, bf16):
     rng = np.random.default_rng(dk * dv)
     n_blk = 7
