@@ -181,11 +181,14 @@ void chunk_kernel(ScanArgs p) {
     constexpr int KPL = CH * SK, VPL = CH * SV;  // lo-plane offsets (fp32 io)
     // Gated DeltaNet's output blocks P: the state waves build them in the first
     // phase, each its share, unless they are few (one wave would build all ten: one
-    // 8K request, 32 heads: 88 -> 72 us with the stagers, two waves 82 -> 79 us) or
+    // 8K request, 32 heads: 81.5 -> 64.8 us with the stagers, two waves 82 -> 79 us) or
     // already do two row tiles' products there -- then the stagers do.  With four
     // state waves of one row tile the stagers' first phase is as long as
-    // theirs, and P there is slower (32K scan 224 -> 233 us)
-    constexpr bool P_STAGERS = FAM == FAM_GDN && !SUMMARY && (RT > 1 || NB <= 2);
+    // theirs, and P there is slower (32K scan 224 -> 233 us).  A 16-token chunk has one
+    // block: the stagers are quicker with it only for a single wave of bf16 tokens
+    // (dk 64 and 128: 0.95 of the time; fp32 dk 64: 1.05, two waves: 1.02 to 1.04)
+    constexpr bool P_STAGERS = FAM == FAM_GDN && !SUMMARY &&
+                               (RT > 1 || (CH == 64 ? NB <= 2 : NB == 1 && !F32IO));
     extern __shared__ __align__(16) char smem[];
 
     const int tid = threadIdx.x;
