@@ -56,22 +56,33 @@ def test_128_rows_match_64(dv, hq, hv, online, monkeypatch):
         assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num()), i
 
 
-@pytest.mark.parametrize("fam,n_seq,nb", [(I.GDN, 17, "4"), (I.GDN, 17, "8"), (I.GDN, 64, "8"), (I.GDN, 65, "8"),
-                                          (I.SSD, 17, "4"), (I.SSD, 33, "4")])
-def test_ranked_segments_match_one_at_a_time(fam, n_seq, nb, monkeypatch):
-    monkeypatch.setenv("LKV_SCAN_NB", nb)
+def _ranked(fam, n_seq, hq, units, n_tok):
+    """Whether the library takes a batch's segments longest first."""
+    return units >= 384 and 1 < n_seq <= 64 and n_tok >= 640 * n_seq and (fam == I.SSD or hq % 8 == 0)
+
+
+# Gated DeltaNet with 64 (nb 4) and 128 (nb 8) state rows per workgroup; Mamba-2 pairs, of
+# which up to 512 are mirrored; 65 segments and 4 heads are not ranked
+@pytest.mark.parametrize("fam,n_seq,hq,hv,dv,nb,units,ranked", [
+    (I.GDN, 17, 8, 16, 128, 4, 544, True), (I.GDN, 17, 8, 16, 256, 8, 544, True), (I.GDN, 64, 8, 8, 128, 8, 512, True),
+    (I.GDN, 65, 8, 8, 128, 8, 520, False), (I.GDN, 64, 4, 8, 128, 8, 512, False),
+    (I.SSD, 25, 1, 32, 64, 4, 400, True), (I.SSD, 33, 2, 32, 64, 4, 528, True), (I.SSD, 64, 1, 16, 64, 4, 512, True),
+    (I.SSD, 65, 1, 16, 64, 4, 520, False)])
+@pytest.mark.parametrize("summary", [False, True])
+def test_ranked_segments_match_one_at_a_time(fam, n_seq, hq, hv, dv, nb, units, ranked, summary, monkeypatch):
+    rows = 128 if fam == I.SSD else 16 * nb
+    assert n_seq * hv * dv // rows == units
     rng = np.random.default_rng(n_seq)
-    lens = [int(x) for x in rng.integers(300, 1400, n_seq)]
-    lens[3] = lens[5] = 700  # equal lengths keep their order
+    lens = [int(x) for x in rng.integers(500, 1400, n_seq)]
+    lens[3] = lens[5] = 900  # equal lengths
     lens[7], lens[11] = 0, 1
-    hv = 16 if n_seq < 60 else 8
-    layer = I.Layer(fam, 2, hv, 128, 128 if fam == I.GDN else 64, 64, "bf16", "bf16" if fam == I.GDN else "f32")
+    layer = I.Layer(fam, hq, hv, 128, dv, 64, "bf16", "bf16" if fam == I.GDN else "f32")
     n = sum(lens)
-    assert n >= 512 * n_seq
+    assert _ranked(fam, n_seq, hq, units, n) == ranked
     g = torch.Generator("cuda").manual_seed(n_seq)
     unit = lambda x: (x / x.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
-    q, k = (unit(torch.randn((n, 2, 128), device="cuda", generator=g)) for _ in range(2))
-    v = torch.randn((n, hv, layer.dv), device="cuda", generator=g).to(torch.bfloat16)
+    q, k = (unit(torch.randn((n, hq, 128), device="cuda", generator=g)) for _ in range(2))
+    v = torch.randn((n, hv, dv), device="cuda", generator=g).to(torch.bfloat16)
     if fam == I.GDN:
         gate = (-0.05 * torch.rand((n, hv), device="cuda", generator=g)).to(torch.bfloat16)
         beta, A = torch.rand((n, hv), device="cuda", generator=g).to(torch.bfloat16), None
@@ -81,21 +92,32 @@ def test_ranked_segments_match_one_at_a_time(fam, n_seq, nb, monkeypatch):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     L = gpu_io.layer_struct(layer)
 
-    def scan(a, b):
+    def run(a, b):
         t0, t1 = int(cu[a]), int(cu[b])
         c = torch.from_numpy(cu[a:b + 1] - cu[a]).cuda()
         part = [None if x is None else x[t0:t1].contiguous() for x in (q, k, v, gate, beta)]
         T = lkv.make_tokens(c, t1 - t0, *part, A)
-        out = torch.full((t1 - t0, hv, layer.dv), 7.0, device="cuda", dtype=torch.bfloat16)
-        S = torch.full((b - a, hv, layer.dv, 128), 7.0, device="cuda")
+        S = torch.full((b - a, hv, dv, 128), 7.0, device="cuda")
+        if summary:
+            M = torch.full((b - a, hv, 128, 128) if fam == I.GDN else (b - a, hv), 7.0, device="cuda")
+            lkv.block_summary(L, T, S, M)
+            return [S, M]
+        out = torch.full((t1 - t0, hv, dv), 7.0, device="cuda", dtype=torch.bfloat16)
         if fam == I.GDN:
             lkv.gdn_chunk_scan(L, T, 0.3, None, out, S)
         else:
             lkv.ssd_chunk_scan(L, T, None, out, S)
-        torch.cuda.synchronize()
-        return out, S
+        return [S, out]
 
-    out, S = scan(0, n_seq)
-    for s in range(n_seq):
-        o1, S1 = scan(s, s + 1)
-        assert torch.equal(out[cu[s]:cu[s + 1]], o1) and torch.equal(S[s], S1[0]), s
+    def pin(fam):
+        if fam == I.GDN:
+            monkeypatch.setenv("LKV_SCAN_NB", str(nb))
+        else:
+            monkeypatch.setenv("LKV_SSD_PAIR", "1")
+
+    pin(fam)
+    S, x = run(0, n_seq)
+    for s in range(n_seq):  # one segment alone is never ranked
+        S1, x1 = run(s, s + 1)
+        assert torch.equal(S[s], S1[0]), s
+        assert torch.equal(x[s] if summary else x[cu[s]:cu[s + 1]], x1[0] if summary else x1), s
