@@ -216,35 +216,41 @@ __device__ __forceinline__ int xcd_unit(int b, int n) {
     return x * q + min(x, r) + i;
 }
 
-// The segment with the rank-th most tokens (ties by index), n_seq <= 64: lane j
-// holds segment j's length, and counts the longer ones.  Every wave computes it
-// for itself, in blocks of 16 segments (a compare and an add each; a taken branch
-// costs as much as a block).  Kernels whose workgroups last as long as their segment
-// take the long segments first, so that a ragged batch does not end on a few
-// long ones.
+// The segment with the rank-th most 64-token chunks (ties by index; above 4094 chunks all
+// count as equal), n_seq <= 64: lane j holds segment j's length, and the candidates are
+// narrowed bit by bit from the top, with scalar operations on the lanes' ballots.  Every
+// wave computes it for itself; about as long for 64 segments as for two (a compare with
+// every other segment took 1.6 us per workgroup at 64).  Kernels whose workgroups last
+// as long as their segment take the long segments first, so that a ragged batch does
+// not end on a few long ones.
 constexpr int RANK_SEGS = 64;
 struct Segment {
     int s;
     int64_t t0, t1;  // its tokens, clamped to [0, n_tok]
 };
 __device__ __forceinline__ Segment ranked_segment(const int32_t* cu, int n_seq, int64_t n_tok, int rank, int lane) {
-    uint32_t key = 0;  // lanes past the last segment stay below every segment
+    constexpr int BITS = 12;
     int32_t a = 0, b = 0;
     if (lane < n_seq) {
         int64_t t0 = cu[lane], t1 = cu[lane + 1];
         t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
         t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-        const int64_t len = t1 - t0 < (1 << 25) ? t1 - t0 : (1 << 25);  // longer ones count as equal
-        key = ((uint32_t)len + 1) * 64 + (63 - lane);
         a = (int32_t)t0;
         b = (int32_t)t1;
     }
-    int longer = 0;
-    for (int k0 = 0; k0 < n_seq; k0 += 16) {
+    const int32_t chunks = (int32_t)(((uint32_t)(b - a) + 63) >> 6);
+    const int32_t key = chunks < (1 << BITS) - 1 ? chunks : (1 << BITS) - 1;
+    uint64_t cand = n_seq < 64 ? (UINT64_C(1) << n_seq) - 1 : ~UINT64_C(0);
+    int left = rank;  // candidates that go before the one wanted
 #pragma unroll
-        for (int k = 0; k < 16; ++k) longer += (uint32_t)__builtin_amdgcn_readlane((int)key, k0 + k) > key ? 1 : 0;
+    for (int bit = BITS - 1; bit >= 0; --bit) {
+        const uint64_t set = cand & __ballot((key >> bit) & 1);
+        const int n = __builtin_popcountll(set);
+        cand = left < n ? set : cand & ~set;
+        left = left < n ? left : left - n;
     }
-    const uint64_t hit = __ballot(lane < n_seq && longer == rank);
+    const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(cand >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cand, 0));
+    const uint64_t hit = cand & __ballot(before == left);
     const int s = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
     return Segment{s, __builtin_amdgcn_readlane(a, s), __builtin_amdgcn_readlane(b, s)};
 }
