@@ -95,6 +95,7 @@ struct ScanArgs {
     int32_t nb;           // B-waves per workgroup (16*nb rows per tile)
     int32_t n_units;
     int32_t ranked;       // longest segments first (see ranked_segment); Gated DeltaNet: dk 128, 4 state waves
+    float times;          // Gated DeltaNet 128-row scan: 64 rows unless twice_rows_pay (0: always 128)
     int32_t wait_limit;   // polls of the solver's bounded wait for the stagers' signals
     // Mamba-2 scan kernel only: with pieces > 1 every segment is cut into that
     // many pieces of whole chunks (the sequence-parallel scan's cut), piece 0
@@ -168,11 +169,11 @@ __device__ __forceinline__ constexpr int low_mt(int j) {
     return mt;
 }
 
+// A workgroup of the grid of n_units, with tiles_b row tiles over dv.
 // RANKED: the longest segments first (see ranked_segment); its own instantiation, as the
 // ranking in the common kernel cost the 32K fold 0.6%
-template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1, bool RANKED = false>
-__global__ __launch_bounds__(64 * (NB + a_waves(FAM, CH, NB, SUMMARY)), (NB + a_waves(FAM, CH, NB, SUMMARY)) / 4)
-void chunk_kernel(ScanArgs p) {
+template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT, bool RANKED>
+__device__ __forceinline__ void chunk_body(const ScanArgs& p, const int n_units, const int tiles_b) {
     static_assert(RT == 1 || (!F32IO && DK >= 32 && CH == 64), "several row tiles per wave: bf16 io, 64-token chunks");
     using Ly = ChunkLds<FAM, DK, CH, F32IO, NB * RT, SUMMARY>;
     constexpr int NTC = CH / 16, NTK = DK / 16;
@@ -216,30 +217,21 @@ void chunk_kernel(ScanArgs p) {
     // one head group of every segment: ragged segment lengths then load the
     // XCDs evenly (giving each XCD whole segments left the fold 13% unbalanced
     // at 32K and the ragged batch 50%).
-    const int tiles = p.tiles_b + p.tiles_m;
+    const int tiles = tiles_b + p.tiles_m;
     const int hr = p.h_v / p.h_qk;  // value heads per q/k head
     const int hpx = (p.h_qk % 8 == 0) ? p.h_qk / 8 : 1;
-    const int u = xcd_unit(blockIdx.x, p.n_units);
+    const int u = xcd_unit(blockIdx.x, n_units);
     const int inner = u % (tiles * hr), outer = u / (tiles * hr);
     const int tile = inner % tiles;
     const int hsub = outer % hpx, o2 = outer / hpx;
-    int s = o2 % p.n_seq;
-    int64_t t0, t1;
-    if constexpr (RANKED) {
-        const Segment sg = ranked_segment(p.cu, p.n_seq, p.n_tok, s, lane);
-        s = sg.s;
-        t0 = sg.t0;
-        t1 = sg.t1;
-    } else {
-        t0 = p.cu[s];
-        t1 = p.cu[s + 1];
-        t0 = t0 < 0 ? 0 : (t0 > p.n_tok ? p.n_tok : t0);
-        t1 = t1 < t0 ? t0 : (t1 > p.n_tok ? p.n_tok : t1);
-    }
+    const Segment sg = RANKED ? ranked_segment(load_segments(p.cu, lane, p.n_seq, p.n_tok), p.n_seq, o2 % p.n_seq)
+                              : plain_segment(p.cu, o2 % p.n_seq, p.n_tok);
+    const int s = sg.s;
+    const int64_t t0 = sg.t0, t1 = sg.t1;
     const int hq = (o2 / p.n_seq) * hpx + hsub;
     const int h = hq * hr + inner / tiles;
-    const bool mtile = tile >= p.tiles_b;
-    const int row0 = (mtile ? tile - p.tiles_b : tile) * 16 * NB * RT;  // first state row of the tile
+    const bool mtile = tile >= tiles_b;
+    const int row0 = (mtile ? tile - tiles_b : tile) * 16 * NB * RT;  // first state row of the tile
     const int nch = (int)((t1 - t0 + CH - 1) / CH);
     const bool with_out = !SUMMARY && p.out != nullptr;
     const bool load_v = SUMMARY ? !mtile : true;  // transition (M) tiles of a block summary skip V
@@ -1221,6 +1213,32 @@ void chunk_kernel(ScanArgs p) {
     }
 }
 
+template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY, int RT = 1, bool RANKED = false>
+__global__ __launch_bounds__(64 * (NB + a_waves(FAM, CH, NB, SUMMARY)), (NB + a_waves(FAM, CH, NB, SUMMARY)) / 4)
+void chunk_kernel(ScanArgs p) {
+    chunk_body<FAM, DK, CH, F32IO, NB, SUMMARY, RT, RANKED>(p, p.n_units, p.tiles_b);
+}
+
+// The Gated DeltaNet scan of 128-row units (four state waves of two row tiles), or of twice
+// as many 64-row ones where the segments' lengths ask for them (one request of 4096 tokens
+// and seven of 512, 32 heads: 253 us with 128 rows, 178 with 64, 177 here; 16 requests of
+// 341-2048: 218, 289 and 219).  Both forms take a CU per workgroup, so one kernel
+// holds both: with 128 rows the grid's second half leaves at once, behind the working
+// half.  The look at the lengths and those workgroups cost 1 to 2 us per round of
+// workgroups.  The 128-row form is bound by its registers (256, 5 or 6 of them spilled;
+// 18 when its branch comes second): the state, two row tiles' outputs and the fragments.
+template <int DK, int CH, bool RANKED>
+__global__ __launch_bounds__(64 * (4 + a_waves(FAM_GDN, CH, 4, false)), (4 + a_waves(FAM_GDN, CH, 4, false)) / 4)
+void gdn_rows_kernel(ScanArgs p) {
+    if (p.times <= 0.f ||
+        twice_rows_pay(p.cu, p.n_seq, p.n_tok, 2 * (p.n_units / p.n_seq), p.times, threadIdx.x & 63)) {
+        if ((int)blockIdx.x < p.n_units)
+            chunk_body<FAM_GDN, DK, CH, false, 4, false, 2, RANKED>(p, p.n_units, p.tiles_b);
+    } else {
+        chunk_body<FAM_GDN, DK, CH, false, 4, false, 1, RANKED>(p, 2 * p.n_units, 2 * p.tiles_b);
+    }
+}
+
 hipError_t launch_scan_gdn(int dk, int chunk, bool f32io, const ScanArgs& a, hipStream_t st);
 hipError_t launch_scan_ssd(int dk, int chunk, bool f32io, const ScanArgs& a, hipStream_t st);
 size_t scan_lds_bytes(int fam, int dk, int chunk, bool f32io, int nb, bool summary);
@@ -1261,6 +1279,18 @@ hipError_t launch_chunk_nb(const ScanArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int DK, int CH>
+hipError_t launch_gdn_rows(const ScanArgs& a, hipStream_t st) {
+    const size_t lds = ChunkLds<FAM_GDN, DK, CH, false, 8, false>::BYTES;
+    auto kern = a.ranked ? gdn_rows_kernel<DK, CH, true> : gdn_rows_kernel<DK, CH, false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.times > 0.f ? 2 * a.n_units : a.n_units),
+                       dim3(64 * (4 + a_waves(FAM_GDN, CH, 4, false))), lds, st, a);
+    return hipGetLastError();
+}
+
 template <int FAM, int DK, int CH, bool F32IO, bool SUMMARY>
 hipError_t launch_chunk_s(const ScanArgs& a, hipStream_t st) {
     switch (a.nb) {
@@ -1271,8 +1301,10 @@ hipError_t launch_chunk_s(const ScanArgs& a, hipStream_t st) {
             // 128 state rows per workgroup: the state-independent work of a chunk is
             // shared by four state waves of two row tiles each, which also share
             // every K (and Q) fragment they read
-            if constexpr ((SUMMARY || FAM == FAM_GDN) && DK == 128 && CH == 64 && !F32IO)
+            if constexpr (SUMMARY && DK == 128 && CH == 64 && !F32IO)
                 return launch_chunk_nb<FAM, DK, CH, F32IO, 4, SUMMARY, 2>(a, st);
+            if constexpr (!SUMMARY && FAM == FAM_GDN && DK == 128 && CH == 64 && !F32IO)
+                return launch_gdn_rows<DK, CH>(a, st);
             return hipErrorInvalidValue;
     }
     return hipErrorInvalidValue;

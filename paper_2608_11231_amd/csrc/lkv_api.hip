@@ -53,13 +53,14 @@ int env_int(const char* name, int dflt) {
 }
 
 // State-row waves per workgroup for the chunk kernels (16*nb rows per
-// workgroup; every workgroup also runs 4 waves for the state-independent
-// work).  More rows per workgroup share that work; fewer give more workgroups.
-// Pick the largest nb that fits LDS and still fills the 256 CUs.  nb = 8 (128 rows:
-// four state waves of two row tiles) takes 4.0 us per chunk where nb = 4 takes 3.2 us
-// for half the rows (dk = 128 scan): one full round of it beats two (16 requests x
-// 32 heads, 512-3072 tokens: 430 -> 290 us; 8 requests of 2048: 218 -> 168 us), while
-// a round it fills only in part loses (6 requests of 512-3072: 131 against 180 us).
+// workgroup; every workgroup also runs a_waves waves -- 4, or 7 beside a single
+// state wave of a Gated DeltaNet scan -- for the state-independent work).  More rows per workgroup share that work; fewer give more workgroups.
+// Pick the largest nb that fits LDS and still fills the 256 CUs.  nb = 8 in a
+// scan (128 rows: four state waves of two row tiles) takes 4.0 us per chunk where nb = 4
+// takes 2.8 us for half the rows (dk = 128): one full round of it beats two (8 requests of
+// 1024 tokens, 32 heads: 118 -> 88 us, 16 of 341-2048: 289 -> 212 us), while a round it
+// fills only in part loses (6 requests of 512-3072: 131 against 180 us).  Lengths that make
+// it lose all the same are seen on the device (gdn_rows_kernel).
 int pick_nw(int fam, int dk, int chunk, bool f32io, int64_t pairs, int rows, int rows2, bool summary) {
     int forced = env_int("LKV_SCAN_NB", 0);
     int fallback = 0;
@@ -212,7 +213,14 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, L->dv, 0, false);
     if (nw == 0) return LKV_E_UNSUPPORTED;
     const int64_t units = pairs * (L->dv / (16 * nw));
-    if (units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;
+    if ((nw == 8 ? 2 : 1) * units >= (INT64_C(1) << 31)) return LKV_E_SHAPE;  // see gdn_rows_kernel
+    // 128 rows, unless the lengths are too uneven: measured against 64 rows over 150 batches
+    // of 240-1024 units, from 1.2 times the chain on never slower (1.2: 0.88-0.99 of the time,
+    // 1.05: 1.08, below 0.6: 1.2-1.3).  Where the q/k heads do not divide over the XCDs,
+    // those do not share the long segments evenly, and 128 rows need segments of half the
+    // longest's length on average (15 heads: 0.73-1.01, but 1.02-1.19 for a mean of 0.35).
+    const float even = (float)units / 256.f;  // half a segment's 64-row units per CU, over all segments
+    a.times = nw != 8 || env_int("LKV_SCAN_NB", 0) ? 0.f : (L->h_qk % 8 == 0 || even < 1.2f ? 1.2f : even);
     a.tiles_b = L->dv / (16 * nw);
     a.tiles_m = 0;
     a.nb = nw;

@@ -216,29 +216,47 @@ __device__ __forceinline__ int xcd_unit(int b, int n) {
     return x * q + min(x, r) + i;
 }
 
-// The segment with the rank-th most 64-token chunks (ties by index; above 4094 chunks all
-// count as equal), n_seq <= 64: lane j holds segment j's length, and the candidates are
-// narrowed bit by bit from the top, with scalar operations on the lanes' ballots.  Every
-// wave computes it for itself; about as long for 64 segments as for two (a compare with
-// every other segment took 1.6 us per workgroup at 64).  Kernels whose workgroups last
-// as long as their segment take the long segments first, so that a ragged batch does
-// not end on a few long ones.
+// A batch's segments across a wave: lane j holds segment j's tokens [t0, t1), clamped to
+// [0, n_tok], and lanes past the last of at most 64 segments an empty range.
 constexpr int RANK_SEGS = 64;
+struct Segments {
+    int32_t t0, t1;
+};
 struct Segment {
     int s;
-    int64_t t0, t1;  // its tokens, clamped to [0, n_tok]
+    int64_t t0, t1;
 };
-__device__ __forceinline__ Segment ranked_segment(const int32_t* cu, int n_seq, int64_t n_tok, int rank, int lane) {
+__device__ __forceinline__ Segments load_segments(const int32_t* cu, int j, int n_seq, int64_t n_tok) {
+    if (j >= n_seq) return Segments{0, 0};
+    int64_t t0 = cu[j], t1 = cu[j + 1];
+    t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
+    t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
+    return Segments{(int32_t)t0, (int32_t)t1};
+}
+__device__ __forceinline__ Segment segment_of(const Segments& sg, int s) {
+    return Segment{s, __builtin_amdgcn_readlane(sg.t0, s), __builtin_amdgcn_readlane(sg.t1, s)};
+}
+// 64-token chunks of this lane's segment
+__device__ __forceinline__ int32_t chunks_of(const Segments& sg) {
+    return (int32_t)(((uint32_t)(sg.t1 - sg.t0) + 63) >> 6);
+}
+// Segment s, in the caller's order
+__device__ __forceinline__ Segment plain_segment(const int32_t* cu, int s, int64_t n_tok) {
+    int64_t t0 = cu[s], t1 = cu[s + 1];
+    t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
+    t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
+    return Segment{s, t0, t1};
+}
+
+// The segment with the rank-th most 64-token chunks (ties by index; above 4094 chunks all
+// count as equal), n_seq <= 64: the candidates are narrowed bit by bit from the top, with
+// scalar operations on the lanes' ballots.  Every wave computes it for itself; about as
+// long for 64 segments as for two (a compare with every other segment took 1.6 us per
+// workgroup at 64).  Kernels whose workgroups last as long as their segment take the
+// long segments first, so that a ragged batch does not end on a few long ones.
+__device__ __forceinline__ Segment ranked_segment(const Segments& sg, int n_seq, int rank) {
     constexpr int BITS = 12;
-    int32_t a = 0, b = 0;
-    if (lane < n_seq) {
-        int64_t t0 = cu[lane], t1 = cu[lane + 1];
-        t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
-        t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-        a = (int32_t)t0;
-        b = (int32_t)t1;
-    }
-    const int32_t chunks = (int32_t)(((uint32_t)(b - a) + 63) >> 6);
+    const int32_t chunks = chunks_of(sg);
     const int32_t key = chunks < (1 << BITS) - 1 ? chunks : (1 << BITS) - 1;
     uint64_t cand = n_seq < 64 ? (UINT64_C(1) << n_seq) - 1 : ~UINT64_C(0);
     int left = rank;  // candidates that go before the one wanted
@@ -251,15 +269,47 @@ __device__ __forceinline__ Segment ranked_segment(const int32_t* cu, int n_seq, 
     }
     const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(cand >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cand, 0));
     const uint64_t hit = cand & __ballot(before == left);
-    const int s = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
-    return Segment{s, __builtin_amdgcn_readlane(a, s), __builtin_amdgcn_readlane(b, s)};
+    return segment_of(sg, __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit)));
 }
-// Segment s, in the caller's order
-__device__ __forceinline__ Segment plain_segment(const int32_t* cu, int s, int64_t n_tok) {
-    int64_t t0 = cu[s], t1 = cu[s + 1];
-    t0 = t0 < 0 ? 0 : (t0 > n_tok ? n_tok : t0);
-    t1 = t1 < t0 ? t0 : (t1 > n_tok ? n_tok : t1);
-    return Segment{s, t0, t1};
+
+// Wave totals (in every lane) of values >= 0
+__device__ __forceinline__ float wave_sum(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_incl_scan(x)), 63));
+}
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp_mov<0x111, 0xf, true>(x));
+    x = fmaxf(x, dpp_mov<0x112, 0xf, true>(x));
+    x = fmaxf(x, dpp_mov<0x114, 0xf, true>(x));
+    x = fmaxf(x, dpp_mov<0x118, 0xf, true>(x));
+    x = fmaxf(x, dpp_mov<0x142, 0xa, false>(x));
+    x = fmaxf(x, dpp_mov<0x143, 0xc, false>(x));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
+}
+
+// Whether a batch gains from workgroups of twice 64 state rows.  They finish more rows per
+// time, but a chunk takes them about 1.4 times as long, so they lose where the longest
+// segment's chain of chunks decides.  With 64 rows the time is at least that chain and the
+// CUs' mean load (a unit counted one chunk longer than its segment); twice the rows pay
+// when the load is `times` the chain.  The lengths are on the device only, so every
+// workgroup decides for itself, all alike.  units: 64-row units per segment.
+__device__ __forceinline__ bool twice_rows_pay(const int32_t* cu, int n_seq, int64_t n_tok, int units, float times,
+                                               int lane) {
+    constexpr float CUS = 256.f;
+    float most = (float)chunks_of(load_segments(cu, lane, n_seq, n_tok)), sum = most;
+    for (int j = lane + 64; j < n_seq; j += 256) {
+        Segments more[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) more[i] = load_segments(cu, j + 64 * i, n_seq, n_tok);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float c = (float)chunks_of(more[i]);
+            most = fmaxf(most, c);
+            sum += c;
+        }
+    }
+    most = wave_max(most);
+    sum = wave_sum(sum);
+    return (sum + n_seq) * units >= times * CUS * (most + 1.f);
 }
 
 // Workgroup barrier for LDS traffic: waits for this wave's LDS operations only,

@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256, 2) void ssd_pair_kernel(ScanArgs p) {
     const bool mirrored = p.ranked && p.n_units <= 512 && blockIdx.x >= 256;
     const int v = mirrored ? p.n_units - 1 - (blockIdx.x - 256) : blockIdx.x;
     const int pr = v % n_pairs;
-    const Segment sg = p.ranked ? ranked_segment(p.cu, p.n_seq, p.n_tok, v / n_pairs, lane)
+    const Segment sg = p.ranked ? ranked_segment(load_segments(p.cu, lane, p.n_seq, p.n_tok), p.n_seq, v / n_pairs)
                               : plain_segment(p.cu, v / n_pairs, p.n_tok);
     const int s = sg.s;
     const int64_t t0 = sg.t0, t1 = sg.t1;

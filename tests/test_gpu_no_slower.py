@@ -41,3 +41,36 @@ def test_composition_of_one_block_is_a_copy():
     t, copy = _times([lambda: lkv.init_compose(L, n, B, Lam, ids, cu, n, S), lambda: lkv.init_single(L, n, B, ids, C)])
     assert torch.equal(S, B) and torch.equal(C, B)
     assert t <= 1.2 * copy, (t, copy)
+
+
+def _gdn(lens, h, d=128):
+    """One Gated DeltaNet layer's scan of requests of these lengths, as a call."""
+    n = sum(lens)
+    g = torch.Generator("cuda").manual_seed(n)
+    unit = lambda x: (x / x.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    q, k = (unit(torch.randn((n, h, d), device="cuda", generator=g)) for _ in range(2))
+    v = torch.randn((n, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    gate = (-0.05 * torch.rand((n, h), device="cuda", generator=g)).to(torch.bfloat16)
+    beta = torch.rand((n, h), device="cuda", generator=g).to(torch.bfloat16)
+    cu = torch.tensor([0, *torch.tensor(lens).cumsum(0).tolist()], dtype=torch.int32, device="cuda")
+    L = lkv.make_layer(lkv.GDN, h, h, d, d, 64)
+    T = lkv.make_tokens(cu, n, q, k, v, gate, beta)
+    out, S = torch.empty_like(v), torch.empty((len(lens), h, d, d), device="cuda")
+    return lambda: lkv.gdn_chunk_scan(L, T, 0.09, None, out, S)
+
+
+@pytest.mark.parametrize("lens", [[4096] + [512] * 7, [256] * 8 + [4096] + [256] * 7])
+def test_one_long_request_among_short_ones(lens, monkeypatch):
+    """The longest request's chain decides: 181 us with 64 state rows per workgroup, 256 us with 128
+    (4096 and seven of 512 tokens, 32 heads).  The call must not take the latter."""
+    scan = _gdn(lens, 32)
+
+    def pinned(nb):
+        def call():
+            monkeypatch.setenv("LKV_SCAN_NB", nb)
+            scan()
+            monkeypatch.delenv("LKV_SCAN_NB")
+        return call
+
+    t, narrow = _times([scan, pinned("4")])
+    assert t <= 1.2 * narrow, (t, narrow)

@@ -437,8 +437,8 @@ def test_gdn_compose_32_blocks(scale):
 def test_dv512_pinned_geometry(fam, nb, monkeypatch):
     """The largest state (dk = 128, dv = 512) in every launch geometry the chunk
     kernels have: 16 nb state rows per workgroup (nb = 8: four waves of two row
-    tiles, block summaries only), i.e. 32 / nb row tiles per head; the scan takes
-    nb up to 4 (eight row tiles per head at dv = 512)."""
+    tiles), i.e. 32 / nb row tiles per head; Mamba-2's scan takes nb up to 4 (eight
+    row tiles per head at dv = 512)."""
     case = GDN_CASES[-1] if fam == I.GDN else SSD_CASES[-1]
     w = _work(fam, case)
     G = gpu_io.GpuWorkload(w)
@@ -451,7 +451,7 @@ def test_dv512_pinned_geometry(fam, nb, monkeypatch):
         assert rel_slices(_np(G.M_pool), M) < STATE_TOL
     else:
         assert np.max(np.abs(_np(G.M_pool) - M) / np.maximum(np.abs(M), 1e-30)) < STATE_TOL
-    monkeypatch.setenv("LKV_SCAN_NB", str(min(nb, 4)))
+    monkeypatch.setenv("LKV_SCAN_NB", str(nb if fam == I.GDN else min(nb, 4)))
     S0 = R.init_compose(w, B, M)
     _scan_check(w, gpu_io.GpuWorkload(w, with_cached=False), S0)
 

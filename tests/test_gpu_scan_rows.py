@@ -1,8 +1,9 @@
 """The Gated DeltaNet scan with 128 state rows per workgroup (two row tiles per
 state wave) against the 64-row form, which computes the same products in the
 same order: bit for bit, on tails, empty and one-token segments, grouped heads,
-pool starts and state-only calls.  And the longest-first order of a ragged
-batch's segments against the segments one at a time."""
+pool starts and state-only calls; and where the segments' lengths choose the form.
+And the longest-first order of a ragged batch's segments against the segments
+one at a time."""
 import numpy as np
 import pytest
 
@@ -121,3 +122,26 @@ def test_ranked_segments_match_one_at_a_time(fam, n_seq, hq, hv, dv, nb, units, 
         S1, x1 = run(s, s + 1)
         assert torch.equal(S[s], S1[0]), s
         assert torch.equal(x[s] if summary else x[cu[s]:cu[s + 1]], x1[0] if summary else x1), s
+
+
+# q/k heads, value heads, dv, lengths, whether the lengths allow 128 rows: one long request
+# among short ones, equal ones, longest last, more than a wave's 64 segments, uneven heads
+@pytest.mark.parametrize("hq,hv,dv,lens", [
+    (8, 32, 128, [70] * 4 + [1500] + [70] * 3), (8, 32, 128, [200] * 8), (16, 16, 256, [65] * 9 + [1, 0, 900]),
+    (8, 8, 128, [40 + i for i in range(70)]), (8, 8, 128, [30] * 69 + [1300]), (15, 30, 128, [150] * 9),
+    (15, 30, 128, [20] * 8 + [600]), (8, 32, 128, [0] * 8)])
+def test_rows_chosen_by_lengths_keep_bits(hq, hv, dv, lens, monkeypatch):
+    assert len(lens) * hv * dv // 128 >= 240  # the batch gets the kernel that holds both forms
+    w = _work(dv, hq, hv, lens)
+    G = gpu_io.GpuWorkload(w, with_cached=False)
+    S0 = _rand(G.S_final.shape, 3)
+    res = []
+    for nb in (None, "4"):
+        if nb:
+            monkeypatch.setenv("LKV_SCAN_NB", nb)
+        for t in (G.out, G.S_final):
+            t.fill_(7.0)
+        G.scan(S0)
+        torch.cuda.synchronize()
+        res.append((G.out.clone(), G.S_final.clone()))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
