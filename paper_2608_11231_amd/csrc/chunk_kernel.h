@@ -95,7 +95,6 @@ struct ScanArgs {
     int32_t nb;           // B-waves per workgroup (16*nb rows per tile)
     int32_t n_units;
     int32_t ranked;       // longest segments first (see ranked_segment); Gated DeltaNet: dk 128, 4 state waves
-    float times;          // Gated DeltaNet 128-row scan: 64 rows unless twice_rows_pay (0: always 128)
     int32_t wait_limit;   // polls of the solver's bounded wait for the stagers' signals
     // Mamba-2 scan kernel only: with pieces > 1 every segment is cut into that
     // many pieces of whole chunks (the sequence-parallel scan's cut), piece 0
@@ -105,6 +104,8 @@ struct ScanArgs {
     int32_t pieces;
     float* piece_B;
     float* piece_L;
+    float times;          // Gated DeltaNet 128-row scan: 64 rows unless twice_rows_pay (0: always 128)
+    PairsRule pairs;      // Mamba-2 pairs: only where pairs_pay; the chunk kernel behind them: only where not
 };
 
 template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY>
@@ -1219,6 +1220,15 @@ void chunk_kernel(ScanArgs p) {
     chunk_body<FAM, DK, CH, F32IO, NB, SUMMARY, RT, RANKED>(p, p.n_units, p.tiles_b);
 }
 
+// Mamba-2 behind ssd_pair_kernel, which leaves the batches to it whose lengths do not suit
+// pairs; its own instantiation, as the look at the lengths in the common kernel made
+// each chunk of a block summary 3% longer
+template <bool SUMMARY, int RT>
+__global__ __launch_bounds__(512, 2) void ssd_unpaired_kernel(ScanArgs p) {
+    if (pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, threadIdx.x & 63)) return;
+    chunk_body<FAM_SSD, 128, 64, false, 4, SUMMARY, RT, false>(p, p.n_units, p.tiles_b);
+}
+
 // The Gated DeltaNet scan of 128-row units (four state waves of two row tiles), or of twice
 // as many 64-row ones where the segments' lengths ask for them (one request of 4096 tokens
 // and seven of 512, 32 heads: 253 us with 128 rows, 178 with 64, 177 here; 16 requests of
@@ -1272,6 +1282,8 @@ hipError_t launch_chunk_nb(const ScanArgs& a, hipStream_t st) {
     auto kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT>;
     if constexpr (FAM == FAM_GDN && DK == 128 && CH == 64 && NB == 4)
         if (a.ranked) kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT, true>;
+    if constexpr (FAM == FAM_SSD && DK == 128 && CH == 64 && NB == 4 && !F32IO)
+        if (a.pairs.halves) kern = ssd_unpaired_kernel<SUMMARY, RT>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -136,32 +136,50 @@ ScanArgs base_args(const lkv_layer* L, const lkv_tokens* T) {
 // bits: the shared chunk kernel, ssd_scan_kernel (eight waves on 64 state rows) and
 // ssd_pair_kernel (two adjacent 64-row units of a group per workgroup), the last
 // two where they cover the shapes (bf16 io, 64-token chunks, dk >= 32, dv a
-// multiple of 64; pairs need an even number of units per group).
+// multiple of 64; pairs need dk = 128 and an even number of units per group).
 // By `units` of 64 rows (segments x heads x dv / 64):
-//  - pairs once every CU has work without them: from one unit per CU at dk = 128
-//    (16 requests x 64 heads of 64 x 128, 512-3072 tokens: 386 -> 213 us; 288
-//    units of 500-1500 tokens: 103 -> 78 us).  At smaller dk two of the chunk kernel's
-//    workgroups share a CU, so pairs wait until they fill a round of two per CU well
-//    (dk 64, 1024 units: 131 -> 88 us, 2048: 237 -> 170 us; 512 units: 68 against 72
-//    us, 1152: 58 against 61 us).  With fewer units the serial chain counts, and
-//    a pair's chunk takes longer (64 units: 52 against 86 us).
+//  - pairs at dk = 128 once every CU has work without them and even lengths can fill the
+//    GPU with them: scans from one unit per CU where a group's units of one segment
+//    nearly fill an XCD (one group, 24 heads and more: the chunk kernel then runs long
+//    segments twice on some CUs; 16 requests x 64 heads of 64 x 128, 512-3072 tokens: 386
+//    -> 213 us), else from three (below, equal lengths gain 10%, ragged ones lose as much to
+//    the second launch); block summaries, whose chunk is half as long, from three.
+//    A pair's chunk takes longer, so they also need even lengths (pairs_rule).  At
+//    smaller dk two of the chunk kernel's workgroups share a CU already and pairs gained
+//    less than the look at the lengths costs (dk 64, 8 heads: 0.92-1.10 of the time up to
+//    3072 units, dk 32: 0.89-1.12).
 //  - ssd_scan_kernel at dk = 128 where the chunk kernel would need a second round
 //    of workgroups (they split rows until they fill the CUs, and overshoot) and
 //    one unit per CU does not: 192 units of 1536 tokens 99 -> 62 us, 96 units 32
 //    -> 22 us.  Within one round the chunk kernel is as fast or faster (64 units:
 //    52 against 58 us, 256 units: 64 against 63 us).
-// LKV_SSD_SCAN_KERNEL=1 forces ssd_scan_kernel, LKV_SSD_PAIR=1 / 0 pairs or none.
+// LKV_SSD_SCAN_KERNEL=1 / 0 forces ssd_scan_kernel or the chunk kernel, LKV_SSD_PAIR=1 / 0
+// pairs or none, and LKV_SCAN_NB (the chunk kernel's rows) the chunk kernel.
 enum SsdKernel { SSD_CHUNK, SSD_SCAN, SSD_PAIR };
 SsdKernel ssd_kernel(const lkv_layer* L, int64_t n_seq, bool summary) {
     if (L->family != LKV_SSD || !ssd_scan_supported(L->dk, L->chunk, L->io_dtype == LKV_F32, L->dv)) return SSD_CHUNK;
-    if (env_int("LKV_SSD_SCAN_KERNEL", 0) == 1) return SSD_SCAN;
+    const int scan = env_int("LKV_SSD_SCAN_KERNEL", -1), pair = env_int("LKV_SSD_PAIR", -1);
+    if (scan >= 0) return scan == 1 ? SSD_SCAN : SSD_CHUNK;
     const int64_t per_group = L->dv / 64 * (int64_t)(L->h_v / L->h_qk), units = n_seq * L->h_qk * per_group;
-    const int forced = env_int("LKV_SSD_PAIR", -1);
-    const bool fills = L->dk == 128 ? units > 256 : (units > 768 && units <= 1024) || units > 1536;
-    if (per_group % 2 == 0 && (forced >= 0 ? forced == 1 : fills)) return SSD_PAIR;
-    if (L->dk != 128 || units > 256 || forced >= 0) return SSD_CHUNK;
+    const bool whole = !summary && L->h_qk == 1 && per_group >= 24;
+    const bool fills = units > (whole ? 256 : 768) && units < (1 << 16) && env_int("LKV_SCAN_NB", 0) == 0;
+    if (L->dk == 128 && per_group % 2 == 0 && (pair >= 0 ? pair == 1 : fills)) return SSD_PAIR;
+    if (L->dk != 128 || units > 256 || pair >= 0 || env_int("LKV_SCAN_NB", 0)) return SSD_CHUNK;
     const int nb = pick_nw(L->family, L->dk, L->chunk, false, n_seq * L->h_v, L->dv, 0, summary);
     return nb > 0 && units * 4 / nb > 256 ? SSD_SCAN : SSD_CHUNK;
+}
+
+// Where pairs pay (see pairs_pay; no halves: forced).  Measured against the chunk kernel over
+// 270 batches, without the second launch: scans at 1.5 chains and above 0.54-0.96 of
+// the time, below 0.92-1.63 (8 heads, one request of 4096 and 35 of 256 tokens: 142 -> 209
+// us); summaries at 2 and above 0.64-0.95, between 1.5 and 2 up to 1.12.
+PairsRule pairs_rule(const lkv_layer* L, bool summary) {
+    PairsRule r = {};
+    if (env_int("LKV_SSD_PAIR", -1) >= 0) return r;
+    r.halves = summary ? 4 : 3;
+    r.units = L->h_v * (L->dv / 64);
+    r.block = r.units / (L->h_qk % 8 == 0 ? 8 : L->h_qk);
+    return r;
 }
 
 // The sequence-parallel Mamba-2 scan as one pass over the pieces plus an
@@ -209,7 +227,11 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     a.S_final = S_final;
     a.summary = 0;
     const SsdKernel sk = ssd_kernel(L, T->n_seq, false);
-    if (sk != SSD_CHUNK) return ssd_scan(L, T, sk, a, (hipStream_t)stream);
+    if (sk == SSD_PAIR) a.pairs = pairs_rule(L, false);
+    if (sk != SSD_CHUNK) {
+        s = ssd_scan(L, T, sk, a, (hipStream_t)stream);
+        if (s != LKV_OK || !a.pairs.halves) return s;  // else the chunk kernel too: one of the two leaves at once
+    }
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, L->dv, 0, false);
     if (nw == 0) return LKV_E_UNSUPPORTED;
     const int64_t units = pairs * (L->dv / (16 * nw));
@@ -220,7 +242,7 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     // those do not share the long segments evenly, and 128 rows need segments of half the
     // longest's length on average (15 heads: 0.73-1.01, but 1.02-1.19 for a mean of 0.35).
     const float even = (float)units / 256.f;  // half a segment's 64-row units per CU, over all segments
-    a.times = nw != 8 || env_int("LKV_SCAN_NB", 0) ? 0.f : (L->h_qk % 8 == 0 || even < 1.2f ? 1.2f : even);
+    if (nw == 8 && !env_int("LKV_SCAN_NB", 0)) a.times = L->h_qk % 8 == 0 || even < 1.2f ? 1.2f : even;
     a.tiles_b = L->dv / (16 * nw);
     a.tiles_m = 0;
     a.nb = nw;
@@ -541,7 +563,11 @@ lkv_status lkv_block_summary(const lkv_layer* L, const lkv_tokens* T, float* B_o
                                             T->A, M_out, st));
     }
     const SsdKernel sk = ssd_kernel(L, T->n_seq, true);
-    if (sk != SSD_CHUNK) return ssd_scan(L, T, sk, a, st);
+    if (sk == SSD_PAIR) a.pairs = pairs_rule(L, true);
+    if (sk != SSD_CHUNK) {
+        s = ssd_scan(L, T, sk, a, st);
+        if (s != LKV_OK || !a.pairs.halves) return s;  // as in chunk_scan
+    }
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, rows_b ? rows_b : rows_m,
                            rows_b ? rows_m : 0, true);
     if (nw == 0) return LKV_E_UNSUPPORTED;

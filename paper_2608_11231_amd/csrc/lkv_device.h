@@ -312,6 +312,78 @@ __device__ __forceinline__ bool twice_rows_pay(const int32_t* cu, int n_seq, int
     return (sum + n_seq) * units >= times * CUS * (most + 1.f);
 }
 
+// The same question for Mamba-2's pairs of units against its chunk kernel, which are two
+// launches: in whole numbers, so that both answer alike (units and chunks below 2^16 and
+// 2^15 in all; the caller sees to the units).  With few B / C groups the chunk kernel's
+// order leaves whole segments on an XCD (units by group, then segment, an eighth of them
+// per XCD), so the load is the busiest XCD's, and pairs pay too when some XCD has more
+// units of three quarters of the longest's chunks than CUs: one of those takes two.
+// Batches of more than 64 segments, whose pairs are not ranked, go by the mean load alone and
+// need half a chain more.
+struct PairsRule {
+    int32_t halves;  // load over the longest chain, in halves, from which pairs pay; 0: always
+    int32_t units;   // 64-row units per segment
+    int32_t block;   // of them adjacent in the order: per group, or per XCD where the groups divide over the XCDs
+};
+template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
+__device__ __forceinline__ int dpp_int(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, BOUND_ZERO);
+}
+__device__ __forceinline__ int wave_incl_scan_int(int x) {
+    x += dpp_int<0x111, 0xf, true>(x);
+    x += dpp_int<0x112, 0xf, true>(x);
+    x += dpp_int<0x114, 0xf, true>(x);
+    x += dpp_int<0x118, 0xf, true>(x);
+    x += dpp_int<0x142, 0xa, false>(x);
+    x += dpp_int<0x143, 0xc, false>(x);
+    return x;
+}
+__device__ __forceinline__ int wave_max_int(int x) {  // of values >= 0
+    x = max(x, dpp_int<0x111, 0xf, true>(x));
+    x = max(x, dpp_int<0x112, 0xf, true>(x));
+    x = max(x, dpp_int<0x114, 0xf, true>(x));
+    x = max(x, dpp_int<0x118, 0xf, true>(x));
+    x = max(x, dpp_int<0x142, 0xa, false>(x));
+    x = max(x, dpp_int<0x143, 0xc, false>(x));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ bool pairs_pay(const int32_t* cu, int n_seq, int64_t n_tok, const PairsRule& rule, int lane) {
+    constexpr int CUS = 256;
+    auto chunks = [&](int j) { return min(chunks_of(load_segments(cu, j, n_seq, n_tok)), (1 << 15) - 2); };
+    int most = chunks(lane);
+    if (n_seq > 64) {
+        int sum = most;
+        for (int j = lane + 64; j < n_seq; j += 64) {
+            const int c = chunks(j);
+            most = max(most, c);
+            sum += c;
+        }
+        most = wave_max_int(most);
+        sum = __builtin_amdgcn_readlane(wave_incl_scan_int(sum), 63);
+        return 2 * (int64_t)(sum + n_seq) * rule.units >= (int64_t)(rule.halves + 1) * CUS * (most + 1);
+    }
+    const bool in = lane < n_seq;
+    const int mine = most;
+    most = wave_max_int(most);
+    // unit t is unit o of segment s's block in group g; lane x looks at XCD x's first unit
+    // and at the weights of the units before it.  Below 2^17 the quotients are exact: (t +
+    // 1/2) / d stays 1 / 2d away from a whole number, many times the rounding
+    const int total = n_seq * rule.units, group = n_seq * rule.block;
+    const int x = min(lane, 8), t = x * (total >> 3) + min(x, total & 7);
+    auto quotient = [](int a, int d) { return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)d)); };
+    const int g = quotient(t, group), in_group = t - g * group, s = quotient(in_group, rule.block);
+    const int o = in_group - s * rule.block;
+    auto lane_of = [](int from, int v) { return __builtin_amdgcn_ds_bpermute(4 * from, v); };
+    auto most_on_xcd = [&](int weight) {  // of a unit of this lane's segment
+        const int incl = wave_incl_scan_int(weight), all = __builtin_amdgcn_readlane(incl, 63);
+        const int before = rule.block * (g * all + lane_of(s, incl - weight)) + o * lane_of(s, weight);
+        const int on = lane_of(lane + 1, before) - before;
+        return wave_max_int(lane < 8 ? on : 0);
+    };
+    return 2 * (int64_t)most_on_xcd(in ? mine + 1 : 0) >= (int64_t)rule.halves * (CUS / 8) * (most + 1) ||
+           most_on_xcd(in && 4 * mine >= 3 * most ? 1 : 0) > CUS / 8;
+}
+
 // Workgroup barrier for LDS traffic: waits for this wave's LDS operations only,
 // so global loads issued before it stay in flight across it (a __syncthreads
 // would also drain them).  Only for barriers that order LDS accesses.

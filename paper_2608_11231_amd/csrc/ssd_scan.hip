@@ -436,6 +436,8 @@ __global__ __launch_bounds__(256, 2) void ssd_pair_kernel(ScanArgs p) {
     // The pairs of a segment are spread over the XCDs: B and C, which they
     // share, are small next to x and y
     const int n_pairs = p.n_units / p.n_seq;
+    // where pairs do not pay, the chunk kernel's launch behind this one takes the batch
+    if (p.pairs.halves && !pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, lane)) return;
     const bool mirrored = p.ranked && p.n_units <= 512 && blockIdx.x >= 256;
     const int v = mirrored ? p.n_units - 1 - (blockIdx.x - 256) : blockIdx.x;
     const int pr = v % n_pairs;
@@ -956,12 +958,7 @@ static hipError_t launch_ssd_pair_t(const ScanArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_ssd_pair(int dk, const ScanArgs& a, hipStream_t st) {
-    switch (dk) {
-        case 32: return launch_ssd_pair_t<32>(a, st);
-        case 64: return launch_ssd_pair_t<64>(a, st);
-        case 128: return launch_ssd_pair_t<128>(a, st);
-    }
-    return hipErrorInvalidValue;
+    return dk == 128 ? launch_ssd_pair_t<128>(a, st) : hipErrorInvalidValue;
 }
 
 hipError_t launch_ssd_scan(int dk, const ScanArgs& a, hipStream_t st) {

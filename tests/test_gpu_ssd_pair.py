@@ -2,8 +2,9 @@
 the shared chunk kernel: the same products in the same order, so scans, block
 summaries (B and Lambda), pool starts and state-only calls must agree bit for
 bit.  Sizes: two heads of 64 rows, two tiles of one head, pairs that straddle
-nothing (grouped heads), every dk, ragged, empty, one-token and chunk-multiple
-segments."""
+nothing (grouped heads), ragged, empty, one-token and chunk-multiple segments; and
+batches on both sides of the rule that chooses between the two from the
+segments' lengths."""
 import numpy as np
 import pytest
 
@@ -20,8 +21,8 @@ from paper_2608_11231_amd import gpu_io, lkv  # noqa: E402
 CASES = [
     # (N, P, G, H, blocks, online)
     (128, 64, 1, 4, ((130, 64), (1, 70), (0,)), (150, 64, 0)),
-    (32, 64, 2, 4, ((100, 0, 65),), (129,)),
-    (64, 128, 1, 3, ((64, 128), (3,)), (0, 191)),
+    (128, 64, 2, 4, ((100, 0, 65),), (129,)),
+    (128, 128, 1, 3, ((64, 128), (3,)), (0, 191)),
     (128, 192, 2, 4, ((65,), (200,), (7,)), (63, 1, 256)),
     (128, 256, 3, 3, ((65, 2),), (320,)),
 ]
@@ -76,8 +77,8 @@ def test_pairs_match_chunk_kernel(case, monkeypatch):
 
 
 # segments x heads on either side of the dispatch's lines: one round of the chunk
-# kernel, ssd_scan_kernel (96 units of dk 128), pairs (more than 256 units), a ragged
-# batch past the segments that are ranked by length, an odd number of units per group
+# kernel, ssd_scan_kernel (96 units of dk 128), pairs (more than 256 units of one group),
+# more segments than are ranked by length, an odd number of units per group
 @pytest.mark.parametrize("n_seq,hq,hv,dv", [(1, 1, 64, 64), (4, 1, 24, 64), (5, 1, 64, 64), (70, 1, 8, 64),
                                             (9, 15, 15, 192)])
 def test_dispatch_keeps_bits(n_seq, hq, hv, dv, monkeypatch):
@@ -94,3 +95,44 @@ def test_dispatch_keeps_bits(n_seq, hq, hv, dv, monkeypatch):
     G.scan(S0)
     torch.cuda.synchronize()
     assert _same(out, G.out) and _same(S, G.S_final)
+
+
+def _batch(hq, hv, dv, lens, seed):
+    layer = I.Layer(I.SSD, hq, hv, 128, dv, 64, "bf16", "f32")
+    law = I.GateLaw(dt_mu=-3.0, dt_bias=-1.0, a_lo=1.0, a_hi=4.0)
+    return gpu_io.GpuWorkload(I.build_workload("len", layer, [[] for _ in lens], list(lens), law, seed),
+                              with_cached=False)
+
+
+# Where pairs may take a batch, two launches follow each other and exactly one works, as the
+# lengths have it: random batches whose longest chain is short, about the line, and long
+@pytest.mark.parametrize("hq,hv,dv,n_seq", [(1, 64, 64, 5), (1, 24, 64, 13), (1, 40, 128, 10), (8, 64, 64, 13),
+                                            (5, 10, 128, 40), (1, 16, 64, 70), (1, 64, 64, 16)])
+def test_lengths_choose_one_launch(hq, hv, dv, n_seq, monkeypatch):
+    units = n_seq * hv * dv // 64
+    assert units > (256 if hq == 1 and hv * dv // 64 >= 24 else 768)
+    rng = np.random.default_rng(units)
+    for draw in range(6):
+        lens = rng.integers(0, (65, 130, 65)[draw % 3], n_seq)
+        if draw % 3:
+            lens[rng.integers(n_seq)] = (200, 900)[draw % 3 - 1]
+        if draw == 3:
+            lens[:] = 64
+        G = _batch(hq, hv, dv, [int(x) for x in lens], draw)
+        S0 = 0.5 * torch.randn(G.S_final.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(draw))
+        T = G.online.struct
+        res = []
+        for pair in (None, "0"):
+            if pair:
+                monkeypatch.setenv("LKV_SSD_PAIR", pair)
+            for t in (G.out, G.S_final):
+                t.fill_(float("nan"))
+            B = torch.full_like(G.S_final, float("nan"))
+            M = torch.full((n_seq, hv), float("nan"), device="cuda")
+            G.scan(S0)
+            lkv.block_summary(G.layer, T, B, M)
+            torch.cuda.synchronize()
+            res.append([x.clone() for x in (G.out, G.S_final, B, M)])
+            monkeypatch.delenv("LKV_SSD_PAIR", raising=False)
+        for a, b in zip(*res):
+            assert torch.equal(_bits(a), _bits(b)) and not bool(a.isnan().any()), (draw, list(lens))
