@@ -105,7 +105,9 @@ struct ScanArgs {
     float* piece_B;
     float* piece_L;
     float times;          // Gated DeltaNet 128-row scan: 64 rows unless twice_rows_pay (0: always 128)
-    PairsRule pairs;      // Mamba-2 pairs: only where pairs_pay; the chunk kernel behind them: only where not
+    // Mamba-2 with ssd_pair_kernel or ssd_scan_kernel: only where pairs_pay, the chunk kernel
+    // behind them only where not
+    PairsRule pairs;
 };
 
 template <int FAM, int DK, int CH, bool F32IO, int NB, bool SUMMARY>
@@ -1220,13 +1222,13 @@ void chunk_kernel(ScanArgs p) {
     chunk_body<FAM, DK, CH, F32IO, NB, SUMMARY, RT, RANKED>(p, p.n_units, p.tiles_b);
 }
 
-// Mamba-2 behind ssd_pair_kernel, which leaves the batches to it whose lengths do not suit
-// pairs; its own instantiation, as the look at the lengths in the common kernel made
-// each chunk of a block summary 3% longer
-template <bool SUMMARY, int RT>
-__global__ __launch_bounds__(512, 2) void ssd_unpaired_kernel(ScanArgs p) {
+// Mamba-2 behind ssd_pair_kernel or ssd_scan_kernel, which leave the batches to it whose
+// lengths do not suit them; its own instantiation, as the look at the lengths in the
+// common kernel made each chunk of a block summary 3% longer
+template <int NB, bool SUMMARY, int RT>
+__global__ __launch_bounds__(64 * (NB + 4), (NB + 4) / 4) void ssd_remaining_kernel(ScanArgs p) {
     if (pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, threadIdx.x & 63)) return;
-    chunk_body<FAM_SSD, 128, 64, false, 4, SUMMARY, RT, false>(p, p.n_units, p.tiles_b);
+    chunk_body<FAM_SSD, 128, 64, false, NB, SUMMARY, RT, false>(p, p.n_units, p.tiles_b);
 }
 
 // The Gated DeltaNet scan of 128-row units (four state waves of two row tiles), or of twice
@@ -1282,8 +1284,8 @@ hipError_t launch_chunk_nb(const ScanArgs& a, hipStream_t st) {
     auto kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT>;
     if constexpr (FAM == FAM_GDN && DK == 128 && CH == 64 && NB == 4)
         if (a.ranked) kern = chunk_kernel<FAM, DK, CH, F32IO, NB, SUMMARY, RT, true>;
-    if constexpr (FAM == FAM_SSD && DK == 128 && CH == 64 && NB == 4 && !F32IO)
-        if (a.pairs.halves) kern = ssd_unpaired_kernel<SUMMARY, RT>;
+    if constexpr (FAM == FAM_SSD && DK == 128 && CH == 64 && (NB == 4 || !SUMMARY) && !F32IO)
+        if (a.pairs.quarters) kern = ssd_remaining_kernel<NB, SUMMARY, RT>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -152,7 +152,9 @@ ScanArgs base_args(const lkv_layer* L, const lkv_tokens* T) {
 //    of workgroups (they split rows until they fill the CUs, and overshoot) and
 //    one unit per CU does not: 192 units of 1536 tokens 99 -> 62 us, 96 units 32
 //    -> 22 us.  Within one round the chunk kernel is as fast or faster (64 units:
-//    52 against 58 us, 256 units: 64 against 63 us).
+//    52 against 58 us, 256 units: 64 against 63 us).  Its chunk takes 7-10% longer, so
+//    with fewer units of a segment than nearly fill an XCD it needs even lengths too
+//    (pairs_rule), and block summaries, which gain 4-14%, don't take it.
 // LKV_SSD_SCAN_KERNEL=1 / 0 forces ssd_scan_kernel or the chunk kernel, LKV_SSD_PAIR=1 / 0
 // pairs or none, and LKV_SCAN_NB (the chunk kernel's rows) the chunk kernel.
 enum SsdKernel { SSD_CHUNK, SSD_SCAN, SSD_PAIR };
@@ -161,23 +163,30 @@ SsdKernel ssd_kernel(const lkv_layer* L, int64_t n_seq, bool summary) {
     const int scan = env_int("LKV_SSD_SCAN_KERNEL", -1), pair = env_int("LKV_SSD_PAIR", -1);
     if (scan >= 0) return scan == 1 ? SSD_SCAN : SSD_CHUNK;
     const int64_t per_group = L->dv / 64 * (int64_t)(L->h_v / L->h_qk), units = n_seq * L->h_qk * per_group;
-    const bool whole = !summary && L->h_qk == 1 && per_group >= 24;
-    const bool fills = units > (whole ? 256 : 768) && units < (1 << 16) && env_int("LKV_SCAN_NB", 0) == 0;
+    const bool whole = L->h_qk == 1 && per_group >= 24;
+    const bool fills = units > (whole && !summary ? 256 : 768) && units < (1 << 16) && env_int("LKV_SCAN_NB", 0) == 0;
     if (L->dk == 128 && per_group % 2 == 0 && (pair >= 0 ? pair == 1 : fills)) return SSD_PAIR;
-    if (L->dk != 128 || units > 256 || pair >= 0 || env_int("LKV_SCAN_NB", 0)) return SSD_CHUNK;
+    if (L->dk != 128 || units > 256 || (summary && !whole) || pair >= 0 || env_int("LKV_SCAN_NB", 0)) return SSD_CHUNK;
     const int nb = pick_nw(L->family, L->dk, L->chunk, false, n_seq * L->h_v, L->dv, 0, summary);
     return nb > 0 && units * 4 / nb > 256 ? SSD_SCAN : SSD_CHUNK;
 }
 
-// Where pairs pay (see pairs_pay; no halves: forced).  Measured against the chunk kernel over
+// Where pairs pay (see pairs_pay; no quarters: forced).  Measured against the chunk kernel over
 // 270 batches, without the second launch: scans at 1.5 chains and above 0.54-0.96 of
 // the time, below 0.92-1.63 (8 heads, one request of 4096 and 35 of 256 tokens: 142 -> 209
 // us); summaries at 2 and above 0.64-0.95, between 1.5 and 2 up to 1.12.
-PairsRule pairs_rule(const lkv_layer* L, bool summary) {
+// ssd_scan_kernel with few units per segment: equal and ragged lengths 0.63-0.77, one long
+// request among short ones (a load of 1.02) up to 1.11.
+PairsRule pairs_rule(const lkv_layer* L, int64_t n_seq, SsdKernel kernel, bool summary) {
     PairsRule r = {};
-    if (env_int("LKV_SSD_PAIR", -1) >= 0) return r;
-    r.halves = summary ? 4 : 3;
-    r.units = L->h_v * (L->dv / 64);
+    const int64_t per_group = L->dv / 64 * (int64_t)(L->h_v / L->h_qk);
+    r.units = (int32_t)(L->h_qk * per_group);
+    if (kernel == SSD_PAIR && env_int("LKV_SSD_PAIR", -1) < 0) {
+        r.quarters = summary ? 8 : 6;
+    } else if (kernel == SSD_SCAN && env_int("LKV_SSD_SCAN_KERNEL", -1) < 0 && !(L->h_qk == 1 && per_group >= 24)) {
+        r.quarters = 5;
+        r.units *= 4 / pick_nw(L->family, L->dk, L->chunk, false, n_seq * L->h_v, L->dv, 0, summary);
+    }
     r.block = r.units / (L->h_qk % 8 == 0 ? 8 : L->h_qk);
     return r;
 }
@@ -227,10 +236,10 @@ lkv_status chunk_scan(const lkv_layer* L, const lkv_tokens* T, float scale, cons
     a.S_final = S_final;
     a.summary = 0;
     const SsdKernel sk = ssd_kernel(L, T->n_seq, false);
-    if (sk == SSD_PAIR) a.pairs = pairs_rule(L, false);
     if (sk != SSD_CHUNK) {
+        a.pairs = pairs_rule(L, T->n_seq, sk, false);
         s = ssd_scan(L, T, sk, a, (hipStream_t)stream);
-        if (s != LKV_OK || !a.pairs.halves) return s;  // else the chunk kernel too: one of the two leaves at once
+        if (s != LKV_OK || !a.pairs.quarters) return s;  // else the chunk kernel too: one of the two leaves at once
     }
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, L->dv, 0, false);
     if (nw == 0) return LKV_E_UNSUPPORTED;
@@ -563,10 +572,10 @@ lkv_status lkv_block_summary(const lkv_layer* L, const lkv_tokens* T, float* B_o
                                             T->A, M_out, st));
     }
     const SsdKernel sk = ssd_kernel(L, T->n_seq, true);
-    if (sk == SSD_PAIR) a.pairs = pairs_rule(L, true);
     if (sk != SSD_CHUNK) {
+        a.pairs = pairs_rule(L, T->n_seq, sk, true);
         s = ssd_scan(L, T, sk, a, st);
-        if (s != LKV_OK || !a.pairs.halves) return s;  // as in chunk_scan
+        if (s != LKV_OK || !a.pairs.quarters) return s;  // as in chunk_scan
     }
     const int nw = pick_nw(L->family, L->dk, L->chunk, f32io, pairs, rows_b ? rows_b : rows_m,
                            rows_b ? rows_m : 0, true);

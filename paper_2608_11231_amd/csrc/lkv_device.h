@@ -319,11 +319,12 @@ __device__ __forceinline__ bool twice_rows_pay(const int32_t* cu, int n_seq, int
 // per XCD), so the load is the busiest XCD's, and pairs pay too when some XCD has more
 // units of three quarters of the longest's chunks than CUs: one of those takes two.
 // Batches of more than 64 segments, whose pairs are not ranked, go by the mean load alone and
-// need half a chain more.
+// need half a chain more.  ssd_scan_kernel's 64-row units against the chunk kernel's
+// of 16 or 32 rows are the same question.
 struct PairsRule {
-    int32_t halves;  // load over the longest chain, in halves, from which pairs pay; 0: always
-    int32_t units;   // 64-row units per segment
-    int32_t block;   // of them adjacent in the order: per group, or per XCD where the groups divide over the XCDs
+    int32_t quarters;  // load over the longest chain, in quarters, from which pairs pay; 0: always
+    int32_t units;     // the chunk kernel's units per segment
+    int32_t block;     // of them adjacent in its order: per group, or per XCD where the groups divide over the XCDs
 };
 template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
 __device__ __forceinline__ int dpp_int(int x) {
@@ -360,7 +361,7 @@ __device__ __forceinline__ bool pairs_pay(const int32_t* cu, int n_seq, int64_t 
         }
         most = wave_max_int(most);
         sum = __builtin_amdgcn_readlane(wave_incl_scan_int(sum), 63);
-        return 2 * (int64_t)(sum + n_seq) * rule.units >= (int64_t)(rule.halves + 1) * CUS * (most + 1);
+        return 4 * (int64_t)(sum + n_seq) * rule.units >= (int64_t)(rule.quarters + 2) * CUS * (most + 1);
     }
     const bool in = lane < n_seq;
     const int mine = most;
@@ -380,7 +381,7 @@ __device__ __forceinline__ bool pairs_pay(const int32_t* cu, int n_seq, int64_t 
         const int on = lane_of(lane + 1, before) - before;
         return wave_max_int(lane < 8 ? on : 0);
     };
-    return 2 * (int64_t)most_on_xcd(in ? mine + 1 : 0) >= (int64_t)rule.halves * (CUS / 8) * (most + 1) ||
+    return 4 * (int64_t)most_on_xcd(in ? mine + 1 : 0) >= (int64_t)rule.quarters * (CUS / 8) * (most + 1) ||
            most_on_xcd(in && 4 * mine >= 3 * most ? 1 : 0) > CUS / 8;
 }
 

@@ -61,8 +61,11 @@ struct SsdLds {
     static constexpr size_t BYTES = SH_OFF + 2 * SH_BUF;
 };
 
-template <int DK>
+// LENGTHS: only where pairs_pay
+template <int DK, bool LENGTHS>
 __global__ __launch_bounds__(512) void ssd_scan_kernel(ScanArgs p) {
+    if constexpr (LENGTHS)
+        if (!pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, threadIdx.x & 63)) return;
     using Ly = SsdLds<DK>;
     constexpr int CH = Ly::CH, NTC = Ly::NTC, NTK = Ly::NTK, NH = Ly::NH;
     constexpr int SK = Ly::SK, SX = Ly::SX, SB = Ly::SB, BLK = Ly::BLK, NPB = Ly::NPB;
@@ -437,7 +440,7 @@ __global__ __launch_bounds__(256, 2) void ssd_pair_kernel(ScanArgs p) {
     // share, are small next to x and y
     const int n_pairs = p.n_units / p.n_seq;
     // where pairs do not pay, the chunk kernel's launch behind this one takes the batch
-    if (p.pairs.halves && !pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, lane)) return;
+    if (p.pairs.quarters && !pairs_pay(p.cu, p.n_seq, p.n_tok, p.pairs, lane)) return;
     const bool mirrored = p.ranked && p.n_units <= 512 && blockIdx.x >= 256;
     const int v = mirrored ? p.n_units - 1 - (blockIdx.x - 256) : blockIdx.x;
     const int pr = v % n_pairs;
@@ -934,7 +937,9 @@ hipError_t launch_ssd_correct(int dk, const SsdCorrectArgs& a, hipStream_t st) {
 template <int DK>
 static hipError_t launch_ssd_scan_t(const ScanArgs& a, hipStream_t st) {
     const size_t lds = SsdLds<DK>::BYTES;
-    auto kern = ssd_scan_kernel<DK>;
+    auto kern = ssd_scan_kernel<DK, false>;
+    if constexpr (DK == 128)
+        if (a.pairs.quarters) kern = ssd_scan_kernel<DK, true>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -104,13 +104,15 @@ def _batch(hq, hv, dv, lens, seed):
                               with_cached=False)
 
 
-# Where pairs may take a batch, two launches follow each other and exactly one works, as the
+# Where pairs or the eight-wave kernel may take a batch, two launches follow each other and exactly one works, as the
 # lengths have it: random batches whose longest chain is short, about the line, and long
 @pytest.mark.parametrize("hq,hv,dv,n_seq", [(1, 64, 64, 5), (1, 24, 64, 13), (1, 40, 128, 10), (8, 64, 64, 13),
-                                            (5, 10, 128, 40), (1, 16, 64, 70), (1, 64, 64, 16)])
+                                            (5, 10, 128, 40), (1, 16, 64, 70), (1, 64, 64, 16),
+                                            (1, 8, 64, 9), (2, 16, 128, 3), (1, 2, 64, 70)])
 def test_lengths_choose_one_launch(hq, hv, dv, n_seq, monkeypatch):
     units = n_seq * hv * dv // 64
-    assert units > (256 if hq == 1 and hv * dv // 64 >= 24 else 768)
+    # pairs, or (a second round of the chunk kernel's small units) the eight-wave kernel
+    assert units > (256 if hq == 1 and hv * dv // 64 >= 24 else 768) or 64 < units < 240
     rng = np.random.default_rng(units)
     for draw in range(6):
         lens = rng.integers(0, (65, 130, 65)[draw % 3], n_seq)
