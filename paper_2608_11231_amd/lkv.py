@@ -102,8 +102,13 @@ def load() -> ctypes.CDLL:
 
 # The smallest calls (a decode step of a few requests, 6 us on the GPU) are bound by
 # this marshalling, so pointers and the stream stay plain integers and the current
-# stream is read without building a torch.cuda.Stream (2.9 -> 0.3 us; a pointer
-# 0.47 -> 0.3 us): decode of four requests 10.2 -> 5.6 us a call.
+# stream is read without building a torch.cuda.Stream where torch has the call for it
+# (2.9 -> 0.3 us; a pointer 0.47 -> 0.3 us): decode of four requests 10.2 -> 7.3 us a
+# call, 5.6 us of it on the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
@@ -116,8 +121,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream):
     if stream is None:
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
