@@ -60,7 +60,8 @@ int env_int(const char* name, int dflt) {
 // takes 2.8 us for half the rows (dk = 128): one full round of it beats two (8 requests of
 // 1024 tokens, 32 heads: 118 -> 88 us, 16 of 341-2048: 289 -> 212 us), while a round it
 // fills only in part loses (6 requests of 512-3072: 131 against 180 us).  Lengths that make
-// it lose all the same are seen on the device (gdn_rows_kernel).
+// it lose all the same are seen on the device (gdn_rows_kernel).  Scans of other dk, of fp32
+// tokens and of dv not a multiple of 128 have no 128-row form: it has not been tried there.
 int pick_nw(int fam, int dk, int chunk, bool f32io, int64_t pairs, int rows, int rows2, bool summary) {
     int forced = env_int("LKV_SCAN_NB", 0);
     int fallback = 0;
@@ -100,10 +101,11 @@ lkv_status check_tokens(const lkv_layer* L, const lkv_tokens* T, bool need_q, bo
 
 // Longest segments first, in the kernels of long workgroups (Gated DeltaNet at dk =
 // 128, one workgroup per CU, and ssd_pair_kernel): where workgroups clearly outnumber
-// the CUs (about one round: the order does not matter, and ranking costs 1.5 us), and the segments average ten 64-token
-// chunks or more (16 requests of 512-3072 tokens, 64-row tiles: 416 -> 395 us; fold of 14
-// blocks of 256-2048 tokens: 156 -> 127 us; but 28 blocks of 64-512 tokens: 81 -> 85
-// us, 64 requests of 20-200: 100 -> 120 us).  The Gated DeltaNet unit order gives each
+// the CUs (about one round: the order does not matter), and the segments average ten
+// 64-token chunks or more, of which ranking costs a fraction (0.5 us a workgroup; with all
+// pairs compared it was 1.5).  Block summaries of 32 heads: 8 and 14 ragged blocks 150 ->
+// 124 and 266 -> 247 us, 14 and 64 equal ones 207 -> 209 and 867 -> 880; 28 blocks of 64-512
+// tokens lost 5%, 64 requests of 20-200 a fifth.  The Gated DeltaNet unit order gives each
 // XCD every segment only when the q/k heads divide over the 8 XCDs; otherwise an
 // XCD's range would hold the long ones and another's the short ones (4 heads, 10
 // requests: 128 -> 139 us).

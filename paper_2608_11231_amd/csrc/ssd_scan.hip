@@ -391,7 +391,7 @@ __global__ __launch_bounds__(512) void ssd_scan_kernel(ScanArgs p) {
 // group (two heads at dv = 64): B and C are staged once for both, the products
 // C B^T are formed once and masked per unit, and each wave holds 32 state rows
 // (all dk columns), so every fragment it reads serves two row tiles and no
-// state parts cross waves.  LDS holds one chunk (69 KB at dk = 128), so two
+// state parts cross waves.  LDS holds one chunk (72 KB at dk = 128), so two
 // workgroups share a CU and cover each other's barriers and load waits; the next
 // chunk waits in registers.  The products are issued in the other kernels' order:
 // identical bits.
